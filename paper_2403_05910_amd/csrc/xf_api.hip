@@ -92,7 +92,7 @@ size_t align_up(size_t b) { return (b + kAlign - 1) / kAlign * kAlign; }
 
 // Workspace carve-up (byte offsets); every piece 256-byte aligned.
 struct Layout {
-    size_t P, Pbar, mx, L, U0, S2, Ly, Lz, V0, V1, V2, lam0, mu, Uf, Pf, Q, G, Lf, Lv, total;
+    size_t P, Pbar, mx, L, U0, S2, V0, V1, V2, lam0, mu, Uf, Pf, Q, G, Lf, Lv, total;
 };
 
 Layout layout(const xf_ctx *c, int op) {
@@ -129,7 +129,7 @@ Layout layout(const xf_ctx *c, int op) {
         l.Lv = o;
         o += align_up(state);
     }
-    if (op == XF_OP_RK3_VJP || (op == XF_OP_RK3 && !mixed)) {
+    if ((op == XF_OP_RK3 || op == XF_OP_RK3_VJP) && !mixed) {   // the directions' sum
         l.L = o;
         o += align_up(state);
     }
@@ -140,12 +140,6 @@ Layout layout(const xf_ctx *c, int op) {
     if (op == XF_OP_RK3) {
         l.S2 = o;
         o += align_up(state);
-        if (!mixed) {
-            l.Ly = o;
-            o += align_up(state);
-            l.Lz = o;
-            o += align_up(state);
-        }
     }
     if (op == XF_OP_RK3_VJP) {
         l.V0 = o;
@@ -313,6 +307,52 @@ int rhs_into(xf_ctx *c, const double *U, double *rhs, const Prim &pb, hipStream_
     double *const all[3] = {rhs, rhs, rhs};
     if ((r = viscous_into(c, U, pb, all, s)) != XF_OK) return r;
     XF_TRY(timed(c, XF_K_ZERO, s, [&] { return xf::launch_zero_ghosts(c->lc, c->nv, rhs, s); }));
+    return XF_OK;
+}
+
+// One SSP-RK3 stage (Eq. 16) from the primitives just computed:
+// out = a U0 + b (in + h L(in)) on the interior, h = *h_dev or dt.  The
+// sweeps run z, y, x; in FP64 contexts every one but the last leaves the sum
+// so far in L and the next adds to it, in mixed ones each writes its FP32
+// buffer; the viscous fluxes go to L (mixed: to Lv) before the last sweep,
+// which finishes the stage (out may be U0, not in).
+int stage_into(xf_ctx *c, const double *in, double *out, const double *U0, double a, double b, double dt,
+               const double *h_dev, const Prim &pb, double *L, double *Lv, hipStream_t s) {
+    const LaunchCtx &lc = c->lc;
+    const int n[3] = {lc.g.nx, lc.g.ny, lc.g.nz};
+    const bool mixed = lc.precision == XF_PREC_MIXED;
+    const int last = n[0] > 1 ? 0 : n[1] > 1 ? 1 : 2;
+    bool any = false;   // L holds something
+    for (int d = 2; d >= last; --d) {
+        if (n[d] <= 1) continue;
+        xf::StageArgs sw{dt, h_dev, c->pp};
+        if (d == last) {
+            if (c->viscous) {
+                double *to = mixed ? Lv : L;
+                if (mixed || !any)
+                    XF_TRY(timed(c, XF_K_ZERO, s, [&] { return xf::launch_zero(lc.g.cells * c->nv, to, s); }));
+                double *const vout[3] = {to, to, to};
+                const int r = viscous_into(c, in, pb, vout, s);
+                if (r != XF_OK) return r;
+                any = true;
+            }
+            sw.Uout = out;
+            sw.U0 = U0;
+            sw.Uin = in;
+            sw.a = a;
+            sw.b = b;
+            if (mixed) {
+                sw.Ly32 = d < 1 && n[1] > 1 ? pb.lf(1) : nullptr;
+                sw.Lz32 = d < 2 && n[2] > 1 ? pb.lf(2) : nullptr;
+                sw.Lv = c->viscous ? Lv : nullptr;
+            }
+        }
+        XF_TRY(timed(c, XF_K_SWEEP_X + d, s, [&] {
+            return c->ops->sweep(lc, d, !mixed && any ? 1 : 0, in, pb.P, pb.Uf, pb.Pf, L, mixed ? pb.lf(d) : nullptr,
+                                 sw, glf_of(c, pb.mx, d), s);
+        }));
+        any = true;
+    }
     return XF_OK;
 }
 
@@ -632,12 +672,8 @@ int xf_cfl_dt(xf_ctx *c, const double *U, double cfl, double *dt_dev, void *ws, 
     return XF_OK;
 }
 
-// One SSP-RK3 step.  Every sweep writes its own residual buffer (stores
-// only: no read-modify-write inside the register-heavy sweep kernels; FP32
-// buffers in mixed contexts, whose sweeps compute the differences in FP32),
-// and a light stage kernel sums them in FP64 and applies the stage
-// combination (ping-pong stage buffers S1, S2; stage 3 writes U in place).  With cfl > 0 the time
-// step is reduced on the device from the stage-1 primitives of U^n and
+// One SSP-RK3 step (ping-pong stage buffers S1, S2; stage 3 writes U in
+// place).  With cfl > 0 the time step is reduced on the device from the stage-1 primitives of U^n and
 // written to *dt_out before it is used.
 int flow_rk3_step(xf_ctx *c, double *U, double dt, const double *dt_in, double cfl, double *dt_out, void *ws,
                   hipStream_t s);
@@ -682,33 +718,12 @@ int flow_rk3_step(xf_ctx *c, double *U, double dt, const double *dt_in, double c
                   hipStream_t s) {
     const Layout l = layout(c, XF_OP_RK3);
     const LaunchCtx &lc = c->lc;
-    const int n[3] = {lc.g.nx, lc.g.ny, lc.g.nz};
     const bool mixed = lc.precision == XF_PREC_MIXED;
     const Prim pb = prim_bufs(c, l, ws);
-    double *P = pb.P;
     double *S1 = at<double>(ws, l.U0), *S2 = at<double>(ws, l.S2);
-    // per-direction residuals: FP64 buffers, or the FP32 ones of a mixed context
-    double *Ld[3] = {nullptr, nullptr, nullptr};
-    if (!mixed) {
-        Ld[0] = at<double>(ws, l.L);
-        Ld[1] = at<double>(ws, l.Ly);
-        Ld[2] = at<double>(ws, l.Lz);
-    }
-    const double *L64[3] = {nullptr, nullptr, nullptr};
-    const float *L32[3] = {nullptr, nullptr, nullptr};
-    for (int d = 0; d < 3; ++d) {
-        if (n[d] <= 1) continue;
-        if (mixed)
-            L32[d] = pb.lf(d);
-        else
-            L64[d] = Ld[d];
-    }
-    // the viscous residual: into each direction's FP64 buffer, or into one
-    // FP64 buffer of its own in a mixed context
+    double *L = mixed ? nullptr : at<double>(ws, l.L);
     double *Lv = mixed && c->viscous ? at<double>(ws, l.Lv) : nullptr;
-    double *const vout[3] = {Lv ? Lv : Ld[0], Lv ? Lv : Ld[1], Lv ? Lv : Ld[2]};
-    const long long nstate = lc.g.cells * c->nv;
-    unsigned long long *mx = at<unsigned long long>(ws, l.mx);
+    unsigned long long *mx = pb.mx;
     const double *h = dt_in;
     double *in[3] = {U, S1, S2};
     double *out[3] = {S1, S2, U};
@@ -730,39 +745,8 @@ int flow_rk3_step(xf_ctx *c, double *U, double dt, const double *dt_in, double c
             XF_TRY(timed(c, XF_K_CFL, s, [&] { return xf::launch_cfl_finish(mx, cfl, dt_out, s); }));
             h = dt_out;
         }
-        // the step size for the positivity blend.  In a mixed context without
-        // viscous terms or the blend the x sweep, which runs last, also
-        // finishes the stage (Eq. 16): measured at 256^3, nine species, the
-        // mixed step gains 0.4 ms, while the FP64 x sweep, at three waves per
-        // SIMD, loses more than the separate stage kernel costs (4.05 against
-        // 2.06 + 1.87 ms), so FP64 keeps that kernel
-        xf::StageArgs sw{dt, h, c->pp};
-        const bool fuse = mixed && !c->viscous && !c->pp && n[0] > 1;
-        if (fuse) {
-            sw.Uout = out[k];
-            sw.U0 = U;
-            sw.Uin = in[k];
-            sw.Ly64 = L64[1];
-            sw.Lz64 = L64[2];
-            sw.Ly32 = L32[1];
-            sw.Lz32 = L32[2];
-            sw.a = a[k];
-            sw.b = b[k];
-        }
-        for (int d = 2; d >= 0; --d) {
-            if (n[d] <= 1) continue;
-            XF_TRY(timed(c, XF_K_SWEEP_X + d, s, [&] {
-                return c->ops->sweep(lc, d, 0, in[k], P, pb.Uf, pb.Pf, Ld[d], mixed ? pb.lf(d) : nullptr, sw,
-                                     glf_of(c, pb.mx, d), s);
-            }));
-        }
-        if (fuse) continue;
-        if (Lv) XF_TRY(timed(c, XF_K_ZERO, s, [&] { return xf::launch_zero(nstate, Lv, s); }));
-        const int r = viscous_into(c, in[k], pb, vout, s);
+        const int r = stage_into(c, in[k], out[k], U, a[k], b[k], dt, h, pb, L, Lv, s);
         if (r != XF_OK) return r;
-        XF_TRY(timed(c, XF_K_STAGE, s, [&] {
-            return c->ops->stage(lc, out[k], U, in[k], L64, L32, Lv, a[k], b[k], dt, h, s);
-        }));
     }
     XF_TRY(fill(c, U, s));
     return XF_OK;
@@ -954,27 +938,20 @@ int xf_rk3_step_vjp(xf_ctx *c, const double *Un, double dt, double *Ubar, void *
     const LaunchCtx &lc = c->lc;
     const long long n = lc.g.cells * c->nv;
     const Prim pb = prim_bufs(c, l, ws);
-    double *P = pb.P, *Pbar = at<double>(ws, l.Pbar), *L = at<double>(ws, l.L);
+    const bool mixed = lc.precision == XF_PREC_MIXED;
+    double *P = pb.P, *Pbar = at<double>(ws, l.Pbar), *L = mixed ? nullptr : at<double>(ws, l.L);
     double *V0 = at<double>(ws, l.V0), *V1 = at<double>(ws, l.V1), *V2 = at<double>(ws, l.V2);
     double *lam0 = at<double>(ws, l.lam0), *mu = at<double>(ws, l.mu);
+    const bool p64 = !mixed || lc.visc == XF_VISC_GLF;
     int r;
     // forward stage states V0 = G(U_n), V1 = G(V0 + dt L(V0)), V2 = G(3/4 V0 + 1/4 (V1 + dt L(V1)))
     XF_TRY(timed(c, XF_K_STAGE, s, [&] { return xf::launch_copy(n, Un, V0, s); }));
     XF_TRY(fill(c, V0, s));
-    if ((r = rhs_into(c, V0, L, pb, s)) != XF_OK) return r;
-    XF_TRY(timed(c, XF_K_STAGE, s, [&] {
-        hipError_t e = xf::launch_copy(n, V0, V1, s);
-        if (e == hipSuccess) e = xf::launch_axpy_state(n, dt, L, 1.0, V1, s);
-        return e;
-    }));
+    XF_TRY(prims(c, V0, pb, s, p64));
+    if ((r = stage_into(c, V0, V1, V0, 0.0, 1.0, dt, nullptr, pb, L, nullptr, s)) != XF_OK) return r;
     XF_TRY(fill(c, V1, s));
-    if ((r = rhs_into(c, V1, L, pb, s)) != XF_OK) return r;
-    XF_TRY(timed(c, XF_K_STAGE, s, [&] {
-        hipError_t e = xf::launch_copy(n, V1, V2, s);
-        if (e == hipSuccess) e = xf::launch_axpy_state(n, dt, L, 1.0, V2, s);
-        if (e == hipSuccess) e = xf::launch_axpy_state(n, 0.75, V0, 0.25, V2, s);
-        return e;
-    }));
+    XF_TRY(prims(c, V1, pb, s, p64));
+    if ((r = stage_into(c, V1, V2, V0, 0.75, 0.25, dt, nullptr, pb, L, nullptr, s)) != XF_OK) return r;
     XF_TRY(fill(c, V2, s));
     // reverse sweep through the stages
     double *const Vs[3] = {V0, V1, V2};

@@ -101,19 +101,19 @@ struct ReactK {
 };
 
 // Step size seen by the sweeps, for the positivity blend: dt, or *dt_dev
-// when dt_dev is set; pp switches the blend on.  With Uout set, the x sweep
-// finishes the SSP-RK3 stage of Eq. 16 itself instead of writing its
-// residual: Uout = a U0 + b (Uin + h L), L = ((L_x + L_y) + L_z) + L_v with
-// its own L_x and the other terms read where their pointers are set (the
-// FP64 or the FP32 per-direction buffers, by the sweep's type), exactly as
-// the separate stage kernel sums them.
+// when dt_dev is set; pp switches the blend on.  With Uout set, the sweep
+// finishes the SSP-RK3 stage of Eq. 16 instead of writing its residual:
+// Uout = a U0 + b (Uin + h L).  FP64 sweeps take Uin from the cells they
+// stage (their input U) and L from their accumulated rhs; mixed ones read
+// Uin, and L = ((d + L_y) + L_z) + L_v from their own difference d, the other
+// directions' FP32 buffers and the viscous residual where set.  Uout may be
+// U0.
 struct StageArgs {
     double dt;
     const double *dt_dev;
     int pp;   // blend the face fluxes for positivity with the step dt (or *dt_dev)
     double *Uout = nullptr;
     const double *U0 = nullptr, *Uin = nullptr;
-    const double *Ly64 = nullptr, *Lz64 = nullptr;
     const float *Ly32 = nullptr, *Lz32 = nullptr;
     const double *Lv = nullptr;
     double a = 0.0, b = 1.0;
@@ -185,14 +185,6 @@ struct NsOps {
     // sub-steps over scale * (dt_dev ? *dt_dev : dt)
     hipError_t (*react)(const LaunchCtx &, double *U, const ReactK *rk, double dt, const double *dt_dev,
                         double scale, int n_sub, hipStream_t);
-    // SSP-RK3 stage on the interior: Uout = a U0 + b (Uin + h (((Lx + Ly) + Lz) + Lv)),
-    // h = dt_dev ? *dt_dev : dt, a == 0 skipping U0; L[d] null for an
-    // inactive direction, FP64 (L64) in FP64 contexts and FP32 (L32) in mixed
-    // ones, Lv (FP64, may be null) the viscous residual of a mixed context.
-    // Uout may alias U0.
-    hipError_t (*stage)(const LaunchCtx &, double *Uout, const double *U0, const double *Uin,
-                        const double *const L64[3], const float *const L32[3], const double *Lv, double a, double b,
-                        double dt, const double *dt_dev, hipStream_t);
 };
 
 // The reaction launcher of one species count, from its own translation unit
@@ -226,8 +218,6 @@ hipError_t launch_rk3_stage_vjp(const LaunchCtx &, int nv, int stage, double *la
 // a mixed context, summed in FP64 in the order of the FP64 sweeps; null for
 // an inactive direction)
 hipError_t launch_sum_dirs(const LaunchCtx &, int nv, double *rhs, const float *const L[3], hipStream_t);
-hipError_t launch_axpy_state(long long n, double a, const double *x, double b, double *y,
-                             hipStream_t);
 hipError_t launch_cfl_reset(unsigned long long *mx, hipStream_t);
 // cell-centred velocity gradient from the velocity fields Q[2..4] of the
 // transport pass: G[3 a + b][cells], fourth-order differences along every

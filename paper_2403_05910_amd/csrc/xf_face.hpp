@@ -40,7 +40,7 @@
 // compiler from hoisting every stencil load to the top of the routine (which
 // holds ~100 loaded values in registers at once); emits no instruction.
 #ifdef __HIP_DEVICE_COMPILE__
-#define XF_FENCE() asm volatile("" ::: "memory")
+#define XF_FENCE() do { asm volatile("" ::: "memory"); __builtin_amdgcn_sched_barrier(0); } while (0)
 #else
 #define XF_FENCE() ((void)0)
 #endif
@@ -69,39 +69,6 @@ XF_HD R e_species(const ThermoK<R> &th, int s, R T) {
            + th.e[s][0];
 }
 
-// WENO5-JS value at the right edge of the cell holding c (linear weights
-// 1/10, 6/10, 3/10; absolute eps = 1e-6; weights (eps + beta)^-2).  Written
-// with one division and with the constant factors gathered where they cost
-// least, none of which changes the weights in exact arithmetic: the
-// smoothness indicators are taken times 12 (13 t^2 + 3 u^2, eps 12e-6), the
-// linear weights times 10 (1, 6, 3), and the candidates times 6, their 1/6
-// applied once to the denominator;
-// alpha_k / sum alpha = d_k prod_{j!=k} s_j / sum(...), s_k = (eps + beta_k)^2.
-// The value as numerator over denominator, N / D.
-XF_HD void weno5_nd(double a, double b, double c, double d, double e, double &N, double &D) {
-    const double q0 = 2.0 * a - 7.0 * b + 11.0 * c;
-    const double q1 = -b + 5.0 * c + 2.0 * d;
-    const double q2 = 2.0 * c + 5.0 * d - e;
-    const double t0 = a - 2.0 * b + c, u0 = a - 4.0 * b + 3.0 * c;
-    const double t1 = b - 2.0 * c + d, u1 = b - d;
-    const double t2 = c - 2.0 * d + e, u2 = 3.0 * c - 4.0 * d + e;
-    double s0 = (13.0 * t0) * t0 + ((3.0 * u0) * u0 + 12e-6);
-    double s1 = (13.0 * t1) * t1 + ((3.0 * u1) * u1 + 12e-6);
-    double s2 = (13.0 * t2) * t2 + ((3.0 * u2) * u2 + 12e-6);
-    s0 *= s0;
-    s1 *= s1;
-    s2 *= s2;
-    const double w0 = s1 * s2, w1 = 6.0 * (s0 * s2), w2 = 3.0 * (s0 * s1);
-    N = w0 * q0 + w1 * q1 + w2 * q2;
-    D = 6.0 * (w0 + w1 + w2);
-}
-
-XF_HD double weno5(double a, double b, double c, double d, double e) {
-    double N, D;
-    weno5_nd(a, b, c, d, e, N, D);
-    return N / D;
-}
-
 // FP64 reciprocal of a positive normal number: the hardware estimate refined
 // by two Newton-Raphson steps r <- r + r (1 - x r) (each step squares the
 // relative error), about 1 ulp, in 5 instructions where the IEEE division
@@ -118,25 +85,16 @@ XF_HD double rcp_nr(double x) {
     return fma(e, r, r);
 }
 
-// Both sides of one characteristic field: weno5(a..e) + weno5(f..j) with one
-// reciprocal, N_p / D_p + N_m / D_m = (N_p D_m + N_m D_p) / (D_p D_m).  With
-// |values| <= v each D lies between 1e-19 ((12e-6)^4) and about 1.5e12 v^8,
-// so D_p D_m and N_p D_m stay finite for v up to about 1e16; past a product
-// of 1e280 (never reached by fluxes at SI scales) the two sides are divided
-// separately.
-XF_HD double weno5_pair(double a, double b, double c, double d, double e, double f, double g, double h,
-                        double i, double j) {
-    double Np, Dp, Nm, Dm;
-    weno5_nd(a, b, c, d, e, Np, Dp);
-    weno5_nd(f, g, h, i, j, Nm, Dm);
-    const double P = Dp * Dm;
-    if (P < 1e280) return (Np * Dm + Nm * Dp) * rcp_nr(P);
-    return Np / Dp + Nm / Dm;
-}
-
-// FP32 form.  The (eps + beta)^2 products can overflow FP32, so the three
-// (eps + beta) are first scaled by the same power of two (exact, no rounding),
-// which leaves the weights unchanged.
+// WENO5-JS value at the right edge of the cell holding c (linear weights
+// 1/10, 6/10, 3/10; absolute eps = 1e-6; weights (eps + beta)^-2), in FP32;
+// the FP64 faces have their own forms (xf_face64.hpp).  One division, and the
+// constant factors gathered where they cost least: the smoothness indicators
+// are taken times 12 (13 t^2 + 3 u^2, eps 12e-6), the linear weights times 10
+// (1, 6, 3), and the candidates times 6, their 1/6 applied once to the
+// denominator; alpha_k / sum alpha = d_k prod_{j!=k} s_j / sum(...),
+// s_k = (eps + beta_k)^2.  Those products can overflow FP32, so the three
+// (eps + beta) are first scaled by the same power of two (exact, no
+// rounding), which leaves the weights unchanged.
 XF_HD float weno5(float a, float b, float c, float d, float e) {
     const float q0 = 2.0f * a - 7.0f * b + 11.0f * c;
     const float q1 = -b + 5.0f * c + 2.0f * d;
@@ -181,28 +139,6 @@ XF_HD R cu6_beta6(R a, R b, R c, R d, R e, R f) {
     const R z3 = d3 + R(-0.3841978250666033) * d4;
     return R(2.2468501984126985) * z0 * z0 + R(3.6320275079835525) * z1 * z1 + R(4.213886137822353) * z2 * z2 +
            R(1.0316113515772065) * z3 * z3 + R(0.03897812227306876) * d4 * d4;
-}
-
-XF_HD double weno_cu6(double a, double b, double c, double d, double e, double f) {
-    const double q0 = (2.0 * a - 7.0 * b + 11.0 * c) * (1.0 / 6.0);
-    const double q1 = (-b + 5.0 * c + 2.0 * d) * (1.0 / 6.0);
-    const double q2 = (2.0 * c + 5.0 * d - e) * (1.0 / 6.0);
-    const double q3 = (11.0 * d - 7.0 * e + 2.0 * f) * (1.0 / 6.0);
-    const double t0 = a - 2.0 * b + c, u0 = a - 4.0 * b + 3.0 * c;
-    const double t1 = b - 2.0 * c + d, u1 = b - d;
-    const double t2 = c - 2.0 * d + e, u2 = 3.0 * c - 4.0 * d + e;
-    const double b0 = (13.0 / 12.0) * t0 * t0 + 0.25 * u0 * u0;
-    const double b1 = (13.0 / 12.0) * t1 * t1 + 0.25 * u1 * u1;
-    const double b2 = (13.0 / 12.0) * t2 * t2 + 0.25 * u2 * u2;
-    const double b6 = cu6_beta6(a, b, c, d, e, f);
-    const double tau = b6 - (b0 + 4.0 * b1 + b2) * (1.0 / 6.0);
-    const double e0 = b0 + 1e-6, e1 = b1 + 1e-6, e2 = b2 + 1e-6, e3 = b6 + 1e-6;
-    const double p01 = e0 * e1, p23 = e2 * e3;
-    const double w0 = (1.0 / 20.0) * (20.0 * e0 + tau) * (e1 * p23);
-    const double w1 = (9.0 / 20.0) * (20.0 * e1 + tau) * (e0 * p23);
-    const double w2 = (9.0 / 20.0) * (20.0 * e2 + tau) * (p01 * e3);
-    const double w3 = (1.0 / 20.0) * (20.0 * e3 + tau) * (p01 * e2);
-    return (w0 * q0 + w1 * q1 + w2 * q2 + w3 * q3) / (w0 + w1 + w2 + w3);
 }
 
 // FP32 form: beta_k + eps and tau are scaled by one power of two (exact),
@@ -273,26 +209,7 @@ XF_HD void weno7_parts(R a, R b, R c, R d, R e, R f, R g, R *q, R *beta) {
     }
 }
 
-// FP64: one division; alpha_k / sum alpha = d_k prod_{j!=k} s_j / sum(...),
-// s_k = (eps + beta_k)^2, after the four (eps + beta_k) are scaled by one
-// power of two (exact; weights unchanged) so that every product is <= 1.
-XF_HD double weno7(double a, double b, double c, double d, double e, double f, double g) {
-    double q[4], be[4];
-    weno7_parts(a, b, c, d, e, f, g, q, be);
-    double e0 = be[0] + 1e-6, e1 = be[1] + 1e-6, e2 = be[2] + 1e-6, e3 = be[3] + 1e-6;
-    int ex;
-    frexp(fmax(fmax(e0, e1), fmax(e2, e3)), &ex);
-    e0 = ldexp(e0, -ex);
-    e1 = ldexp(e1, -ex);
-    e2 = ldexp(e2, -ex);
-    e3 = ldexp(e3, -ex);
-    const double s0 = e0 * e0, s1 = e1 * e1, s2 = e2 * e2, s3 = e3 * e3;
-    const double p01 = s0 * s1, p23 = s2 * s3;
-    const double w0 = s1 * p23, w1 = 12.0 * (s0 * p23), w2 = 18.0 * (p01 * s3), w3 = 4.0 * (p01 * s2);
-    return (w0 * q[0] + w1 * q[1] + w2 * q[2] + w3 * q[3]) / (12.0 * (w0 + w1 + w2 + w3));
-}
-
-// FP32: the three-factor products of the FP64 form can underflow FP32 when
+// The three-factor products of a one-division form can underflow FP32 when
 // one sub-stencil is far rougher than the others, so the weights are taken
 // as d_k / (eps + beta_k)^2 directly, after the (eps + beta_k) are scaled by
 // the power of two of the smallest (exact): every 1 / (eps + beta_k) is then
@@ -363,10 +280,10 @@ struct Axes {
     static constexpr int t2 = (DIR == 2) ? 1 : 2;
 };
 
-// Numerical flux at one face.  Each component of F^ is handed to out(q, v)
-// as soon as it is final (species first, then momentum and energy), so the
+// Numerical flux at one face.  Each component of F^ is handed to out.put as
+// soon as it is final (species first, then momentum and energy), so the
 // caller decides where it lives.  flags collects XF_FLAG_C2 if the face c^2
-// is not positive.  FENCE inserts compiler fences between the phases.
+// is not positive.
 // Artificial viscosity of the flux splitting (Eq. 14; Table I): LLF, the
 // max over the stencil cells of each field's |lambda|; ROE, |lambda| of
 // the face's Roe state (u~_n - c~, u~_n, u~_n + c~); GLF, each field's
@@ -393,16 +310,14 @@ constexpr int stencil_radius(int rec) { return rec == kReconWeno7 ? 4 : 3; }
 // values of the stencil cells: WENO5-JS of g+ on cells i-2..i+2 plus g-
 // mirrored on i+3..i-1; WENO-CU6 of both on all six cells; WENO7-JS of g+
 // on i-3..i+3 plus g- mirrored on i+4..i-2.
-template <int REC, bool PAIR, typename R>
-XF_HD R recon_pair(const R *gp, const R *gm) {
+template <int REC>
+XF_HD float recon_pair(const float *gp, const float *gm) {
     if constexpr (REC == kReconWeno7)
         return weno7(gp[0], gp[1], gp[2], gp[3], gp[4], gp[5], gp[6]) +
                weno7(gm[7], gm[6], gm[5], gm[4], gm[3], gm[2], gm[1]);
     else if constexpr (REC == kReconCu6)
         return weno_cu6(gp[0], gp[1], gp[2], gp[3], gp[4], gp[5]) +
                weno_cu6(gm[5], gm[4], gm[3], gm[2], gm[1], gm[0]);
-    else if constexpr (sizeof(R) == 8 && PAIR)
-        return weno5_pair(gp[0], gp[1], gp[2], gp[3], gp[4], gm[5], gm[4], gm[3], gm[2], gm[1]);
     else
         return weno5(gp[0], gp[1], gp[2], gp[3], gp[4]) + weno5(gm[5], gm[4], gm[3], gm[2], gm[1]);
 }
@@ -410,15 +325,13 @@ XF_HD R recon_pair(const R *gp, const R *gm) {
 // SPD (kVisc*) and REC (kRecon*) select the artificial viscosity and the
 // reconstruction at compile time, so every combination is its own code with
 // no run-time switch left in it (ROE and GLF skip the stencil maxima
-// altogether); ds supplies the GLF speeds.  PAIR takes both sides of an
-// FP64 WENO5 field with one reciprocal (off where the extra live values
-// spill, as next to the positivity blend).  ROLL runs the species loops as
-// loops (the Roe Y_s and chi_s recomputed where used, the per-cell sums
-// taken species by species) instead of unrolling them, which frees the
-// per-species registers at the cost of three evaluations of e_s(T~) per
-// species instead of one.
-template <int NS, typename R, int DIR, bool FENCE = false, int SPD = kViscLlf, int REC = kReconWeno5,
-          bool PAIR = true, bool ROLL = false, class St, class Out>
+// altogether); ds supplies the GLF speeds.  The species loops run as loops
+// (the Roe Y_s and chi_s recomputed where used, the per-cell sums taken
+// species by species), which frees the per-species registers at the cost of
+// three evaluations of e_s(T~) per species instead of one.  FP32 only: its
+// operations and their order are kept as they are, because another rounding
+// in FP32 changes the state in the eighth digit.
+template <int NS, typename R, int DIR, int SPD, int REC, class St, class Out>
 XF_HD void face_flux_to(const St &st, const ThermoK<R> &th, Out &&out, unsigned &flags, const Dissip &ds) {
     constexpr int RAD = stencil_radius(REC);
     constexpr int W = 2 * RAD;       // stencil cells
@@ -446,81 +359,48 @@ XF_HD void face_flux_to(const St &st, const ThermoK<R> &th, Out &&out, unsigned 
     for (int k = 0; k < 3; ++k) ut[k] = aL * R(st.u(IM + k, CL)) + aR * R(st.u(IM + k, CR));
     const R Ht = aL * (R(st.u(IE, CL)) + R(st.p(1, CL))) + aR * (R(st.u(IE, CR)) + R(st.p(1, CR)));
     const R Tt = wL * R(st.p(0, CL)) + wR * R(st.p(0, CR));
-    R Yt[ROLL ? 1 : NS], chi[ROLL ? 1 : NS];   // per-species Roe values (unrolled form only)
     R Rb = R(0), cvb = R(0), Se = R(0), S1 = R(0);
-    if constexpr (ROLL) {
 #pragma unroll 1
-        for (int s = 0; s < NS; ++s) {
-            const R Y = aL * R(st.u(s, CL)) + aR * R(st.u(s, CR));
-            S1 += Y;
-            Rb += Y * th.Rs[s];
-            cvb += Y * cv_species(th, s, Tt);
-            Se += Y * e_species(th, s, Tt);
-        }
-    } else {
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            Yt[s] = aL * R(st.u(s, CL)) + aR * R(st.u(s, CR));
-            Rb += Yt[s] * th.Rs[s];
-            cvb += Yt[s] * cv_species(th, s, Tt);
-            chi[s] = e_species(th, s, Tt);   // e_s(T~) for now
-        }
+    for (int s = 0; s < NS; ++s) {
+        const R Y = aL * R(st.u(s, CL)) + aR * R(st.u(s, CR));
+        S1 += Y;
+        Rb += Y * th.Rs[s];
+        cvb += Y * cv_species(th, s, Tt);
+        Se += Y * e_species(th, s, Tt);
     }
     const R Gam = Rb / cvb;
     const R q2 = ut[0] * ut[0] + ut[1] * ut[1] + ut[2] * ut[2];
     R c2 = Gam * (Ht - q2);
-    if constexpr (ROLL) {
-        // sum_s Y_s chi_s with S1 = sum Y, Se = sum Y e_s(T~), Rb = sum Y R_s
-        c2 += Gam * (R(0.5) * q2 * S1 - Se) + Tt * Rb;
-    } else {
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            chi[s] = Gam * (R(0.5) * q2 - chi[s]) + th.Rs[s] * Tt;
-            c2 += Yt[s] * chi[s];
-        }
-    }
+    // sum_s Y_s chi_s with S1 = sum Y, Se = sum Y e_s(T~), Rb = sum Y R_s
+    c2 += Gam * (R(0.5) * q2 * S1 - Se) + Tt * Rb;
     if (!(c2 > R(0))) flags |= XF_FLAG_C2;
     const R ct = xsqrt(c2);
     const R ic2 = R(1) / c2;
     const R cih = R(0.5) * ct * ic2;      // c / (2 c^2)
     const R utn = ut[Axes<DIR>::n], ut1 = ut[Axes<DIR>::t1], ut2 = ut[Axes<DIR>::t2];
 
-    if (FENCE) XF_FENCE();
     // ---- 2./3. per-cell scalars of the projections, LLF speeds ----------
     R un[W], DU[W], DF[W], rh[W];
     R aM = R(0), a0 = R(0), aP = R(0);
-    R scm[ROLL ? W : 1];   // rolled form: sum_s chi_s rho_s of every cell, species outermost
-    if constexpr (ROLL) {
+    R scm[W];   // sum_s chi_s rho_s of every cell, species outermost
+#pragma unroll
+    for (int m = 0; m < W; ++m) {
+        scm[m] = R(0);
+        rh[m] = R(0);
+    }
+#pragma unroll 1
+    for (int s = 0; s < NS; ++s) {
+        const R chis = Gam * (R(0.5) * q2 - e_species(th, s, Tt)) + th.Rs[s] * Tt;
 #pragma unroll
         for (int m = 0; m < W; ++m) {
-            scm[m] = R(0);
-            rh[m] = R(0);
-        }
-#pragma unroll 1
-        for (int s = 0; s < NS; ++s) {
-            const R chis = Gam * (R(0.5) * q2 - e_species(th, s, Tt)) + th.Rs[s] * Tt;
-#pragma unroll
-            for (int m = 0; m < W; ++m) {
-                const R r = R(st.u(s, m));
-                scm[m] += chis * r;
-                rh[m] += r;
-            }
+            const R r = R(st.u(s, m));
+            scm[m] += chis * r;
+            rh[m] += r;
         }
     }
 #pragma unroll
     for (int m = 0; m < W; ++m) {
-        R sc = R(0), sr = R(0);
-        if constexpr (ROLL) {
-            sc = scm[m];
-            sr = rh[m];
-        } else {
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                const R r = R(st.u(s, m));
-                sc += chi[s] * r;
-                sr += r;
-            }
-        }
+        const R sc = scm[m];
         const R rinv = R(st.p(3, m)), pm = R(st.p(1, m)), cm = R(st.p(2, m));
         const R E = R(st.u(IE, m));
         const R unm = R(st.u(IN, m)) * rinv;
@@ -531,7 +411,6 @@ XF_HD void face_flux_to(const St &st, const ThermoK<R> &th, Out &&out, unsigned 
         un[m] = unm;
         DU[m] = dpU * ic2;
         DF[m] = dpF * ic2;
-        rh[m] = sr;
         if constexpr (SPD == kViscLlf) {
             aM = rmax(aM, rabs(unm - cm));
             a0 = rmax(a0, rabs(unm));
@@ -554,7 +433,6 @@ XF_HD void face_flux_to(const St &st, const ThermoK<R> &th, Out &&out, unsigned 
         aP = R(ds.alpha[2 * ds.astride + ds.fidx]);
     }
 
-    if (FENCE) XF_FENCE();
     // ---- acoustic pair ----------------------------------------------------
     R hm, hp;
     {
@@ -571,12 +449,11 @@ XF_HD void face_flux_to(const St &st, const ThermoK<R> &th, Out &&out, unsigned 
             gPp[m] = R(0.5) * (wFp + aP * wUp);
             gPm[m] = R(0.5) * (wFp - aP * wUp);
         }
-        hm = recon_pair<REC, PAIR>(gMp, gMm);
-        hp = recon_pair<REC, PAIR>(gPp, gPm);
+        hm = recon_pair<REC>(gMp, gMm);
+        hp = recon_pair<REC>(gPp, gPm);
     }
     const R Asum = hm + hp, Dif = hp - hm;
 
-    if (FENCE) XF_FENCE();
     // ---- tangential pair --------------------------------------------------
     R h1, h2;
     {
@@ -588,7 +465,7 @@ XF_HD void face_flux_to(const St &st, const ThermoK<R> &th, Out &&out, unsigned 
             gp[m] = R(0.5) * (wF + a0 * wU);
             gm[m] = R(0.5) * (wF - a0 * wU);
         }
-        h1 = recon_pair<REC, PAIR>(gp, gm);
+        h1 = recon_pair<REC>(gp, gm);
 #pragma unroll
         for (int m = 0; m < W; ++m) {
             const R wU = R(st.u(I2, m)) - ut2 * rh[m];
@@ -596,7 +473,7 @@ XF_HD void face_flux_to(const St &st, const ThermoK<R> &th, Out &&out, unsigned 
             gp[m] = R(0.5) * (wF + a0 * wU);
             gm[m] = R(0.5) * (wF - a0 * wU);
         }
-        h2 = recon_pair<REC, PAIR>(gp, gm);
+        h2 = recon_pair<REC>(gp, gm);
     }
 
     // ---- species fields, back-projected as they come ----------------------
@@ -613,24 +490,15 @@ XF_HD void face_flux_to(const St &st, const ThermoK<R> &th, Out &&out, unsigned 
             gp[m] = R(0.5) * (wF + a0 * wU);
             gm[m] = R(0.5) * (wF - a0 * wU);
         }
-        const R hs = recon_pair<REC, PAIR>(gp, gm);
-        out(s, Ys * Asum + hs);
+        const R hs = recon_pair<REC>(gp, gm);
+        out.template put<0>(s, Ys * Asum + hs);
         gsum += hs;
         gE += (q2 - chis * iGam) * hs;
     };
-    if constexpr (ROLL) {
 #pragma unroll 1
-        for (int s = 0; s < NS; ++s) {
-            if (FENCE) XF_FENCE();
-            const R Ys = aL * R(st.u(s, CL)) + aR * R(st.u(s, CR));
-            species(s, Ys, Gam * (R(0.5) * q2 - e_species(th, s, Tt)) + th.Rs[s] * Tt);
-        }
-    } else {
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            if (FENCE) XF_FENCE();
-            species(s, Yt[s], chi[s]);
-        }
+    for (int s = 0; s < NS; ++s) {
+        const R Ys = aL * R(st.u(s, CL)) + aR * R(st.u(s, CR));
+        species(s, Ys, Gam * (R(0.5) * q2 - e_species(th, s, Tt)) + th.Rs[s] * Tt);
     }
 
     // ---- momentum and energy of F^ = R h ----------------------------------
@@ -640,16 +508,10 @@ XF_HD void face_flux_to(const St &st, const ThermoK<R> &th, Out &&out, unsigned 
     Fm[Axes<DIR>::n] += ct * Dif;
     Fm[Axes<DIR>::t1] += h1;
     Fm[Axes<DIR>::t2] += h2;
-    out(IM + 0, Fm[0]);
-    out(IM + 1, Fm[1]);
-    out(IM + 2, Fm[2]);
-    out(IE, Ht * Asum + utn * ct * Dif + ut1 * h1 + ut2 * h2 + gE);
-}
-
-// Numerical flux at one face into Fh[0..NS+3] (conservative field order).
-template <int NS, typename R, int DIR>
-XF_HD void face_flux(const Stencil &st, const ThermoK<R> &th, R *__restrict__ Fh, unsigned &flags) {
-    face_flux_to<NS, R, DIR>(st, th, [&](int q, R v) { Fh[q] = v; }, flags, Dissip{kViscLlf, nullptr});
+    out.template put<0>(IM + 0, Fm[0]);
+    out.template put<0>(IM + 1, Fm[1]);
+    out.template put<0>(IM + 2, Fm[2]);
+    out.template put<0>(IE, Ht * Asum + utn * ct * Dif + ut1 * h1 + ut2 * h2 + gE);
 }
 
 // ---------------------------------------------------------------------------

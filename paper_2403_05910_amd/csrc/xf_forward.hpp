@@ -4,10 +4,9 @@
 //   k_sweep_x     x-direction flux difference, one face per thread
 //   k_sweep_tile  y/z-direction flux difference, tiles of one face per thread
 //   k_cfl         CFL reduction (Eq. 17), wavefront max + one 64-bit atomic
-//   k_stage_sum   SSP-RK3 stage (Eq. 16) from the per-direction residuals
 #pragma once
 
-#include "xf_face.hpp"
+#include "xf_face64.hpp"
 
 namespace xf {
 
@@ -222,31 +221,6 @@ __global__ __launch_bounds__(256) void k_prims(const double *U, double *__restri
     }
 }
 
-// SSP-RK3 stage of Eq. 16 on the interior cells: Uout = a U0 + b (Uin + h L),
-// L = ((Lx + Ly) + Lz) + Lv.  A block takes one interior row of one field
-// (blockIdx.x = j + ny k, blockIdx.y = field), its threads the cells along
-// x, so no index needs a 64-bit division.
-template <typename LT>
-__global__ __launch_bounds__(256) void k_stage_sum(double *Uout, const double *U0, const double *Uin, const LT *Lx,
-                                                   const LT *Ly, const LT *Lz, const double *Lv, Geo g, double a,
-                                                   double b, double dt, const double *dt_dev) {
-    const int row = blockIdx.x;
-    const int j = row % g.ny, k = row / g.ny;
-    const long long base = (long long)blockIdx.y * g.cells + (long long)(g.gz + k) * g.sz +
-                           (long long)(g.gy + j) * g.sy + g.gx;
-    const double h = dt_dev ? *dt_dev : dt;
-    for (int i = threadIdx.x; i < g.nx; i += blockDim.x) {
-        const long long o = base + i;
-        double L = 0.0;
-        if (Lx) L = (double)Lx[o];
-        if (Ly) L = L + (double)Ly[o];
-        if (Lz) L = L + (double)Lz[o];
-        if (Lv) L = L + Lv[o];
-        const double v = Uin[o] + h * L;
-        Uout[o] = a == 0.0 ? b * v : a * U0[o] + b * v;
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Phase fences, loop form and occupancy per kernel flavour, chosen from the
 // compiler's resource report and timings at 256^3, nine species:
@@ -259,20 +233,10 @@ __global__ __launch_bounds__(256) void k_stage_sum(double *Uout, const double *U
 //   blended step went from 37.5 to 47.7 ms), the FP64 WENO7 instances at
 //   one (at two they spilled 324-460 bytes per lane; at one they keep their
 //   overflow in the accumulation registers, 61.7 -> 50.3 ms per step).
-template <typename R>
-struct SweepTune {
-    static constexpr bool fence_face = false;   // face-per-thread sweeps (x, tiled y/z)
-    static constexpr bool roll_tile = true;     // species loops rolled in the y/z tiles
-};
-template <>
-struct SweepTune<double> {
-    static constexpr bool fence_face = true;
-    static constexpr bool roll_tile = true;
-};
 // Waves per SIMD asked of a face-per-thread sweep (X: the x sweep).
 template <typename R, int REC, bool X, bool PP>
 constexpr int sweep_waves() {
-    if (sizeof(R) == 4) return X ? 4 : 1;
+    if (sizeof(R) == 4) return X ? 4 : (!PP && REC == kReconWeno5) ? 5 : 1;
     if (REC == kReconWeno7) return 1;
     if (!X && !PP && REC == kReconWeno5) return 3;     // the exchanging FP64 tiles (CU6 spills at three)
     return (X && !PP && REC == kReconWeno5) ? 3 : 2;   // the rolled CU6 x face spills ~100 bytes at three
@@ -286,12 +250,155 @@ __device__ __forceinline__ R pp_lambda(const Geo &g, const StageArgs &sa, double
     return R(D * h * idx);
 }
 
-// Write the finished residual d of one field at one cell: rhs = d, or
-// rhs += d when accumulating (FP64 output only; an FP32 difference is stored
-// as computed, exactly).
-template <typename OT>
-__device__ __forceinline__ void put_result(OT *__restrict__ rhs, long long o, double d, int accumulate) {
-    rhs[o] = accumulate ? OT(rhs[o] + d) : OT(d);
+// Where a sweep's flux differences go.  kStore: to rhs; kAdd: added to what
+// an earlier direction left in rhs; kFinish: the last sweep of an RK3 stage
+// finishes it, Uout = a U0 + b (Uin + h L) with L the sum of the directions.
+// FP64 sweeps accumulate L in rhs and take Uin from the staged stencil; the
+// mixed ones keep one FP32 buffer per direction and read Uin in FP64.  The
+// separate stage kernel this replaced moved 10.4 GB per stage at 256^3, nine
+// species (1.85 ms), most of it read again from what the sweeps had just
+// touched.  What bounds the finish is the latency of its loads: load() runs a
+// component ahead of put() in the exchanging sweeps, and for all components
+// at once where the block's fluxes wait in LDS.  The exchanging sweeps take
+// the mode as a template argument and load without a branch (an address that
+// is not needed is replaced by one that is, its value multiplied by zero):
+// with run-time switches around each component the z sweep, which only
+// stores, took 1.85 ms instead of 1.57.  kByArgs: read from the arguments.
+constexpr int kByArgs = -1, kStore = 0, kAdd = 1, kFinish = 2;
+template <typename R, int MODE>
+struct CellOut {
+    // what one cell and field needs from memory
+    struct Held {
+        double L = 0.0, U0 = 0.0;              // FP64: the directions summed so far
+        double Uin = 0.0, Lv = 0.0;            // mixed
+        float Ly = 0.0f, Lz = 0.0f;
+    };
+    R *rhs;
+    const StageArgs &sa;
+    const double *pL, *p0;                     // FP64 kFinish: where L and U0 are read
+    double h, fL;                              // fL: 1 when L is read, 0 when this sweep is the only one
+    int accumulate;
+    __device__ __forceinline__ CellOut(R *r, const StageArgs &s, int acc)
+        : rhs(r), sa(s), h(!s.Uout ? 0.0 : s.dt_dev ? *s.dt_dev : s.dt), accumulate(acc) {
+        if constexpr (sizeof(R) == 8 && MODE == kFinish) {
+            pL = acc ? rhs : s.Uin;
+            p0 = s.a != 0.0 ? s.U0 : pL;
+            fL = acc ? 1.0 : 0.0;
+        }
+    }
+    __device__ __forceinline__ bool finish() const { return MODE == kByArgs ? sa.Uout != nullptr : MODE == kFinish; }
+    __device__ __forceinline__ bool add() const { return MODE == kByArgs ? accumulate != 0 : MODE == kAdd; }
+    __device__ __forceinline__ void load(long long o, Held &v) const {
+        if constexpr (sizeof(R) == 8 && MODE == kFinish) {
+            v.L = pL[o];
+            v.U0 = p0[o];
+            return;
+        }
+        if constexpr (sizeof(R) == 8) {
+            if (add()) v.L = rhs[o];
+        } else if (finish()) {
+            v.Uin = sa.Uin[o];
+            if (sa.Ly32) v.Ly = sa.Ly32[o];
+            if (sa.Lz32) v.Lz = sa.Lz32[o];
+            if (sa.Lv) v.Lv = sa.Lv[o];
+        }
+        if (finish() && sa.a != 0.0) v.U0 = sa.U0[o];
+    }
+    // d: the flux difference of this sweep; Uin: the stage input (FP64 sweeps)
+    __device__ __forceinline__ void put(long long o, double d, double Uin, const Held &v) const {
+        if constexpr (sizeof(R) == 8 && MODE == kFinish) {
+            sa.Uout[o] = sa.a * v.U0 + sa.b * (Uin + h * (fL * v.L + d));
+            return;
+        }
+        if constexpr (sizeof(R) == 8) {
+            if (add()) d = v.L + d;
+        } else if (finish()) {
+            if (sa.Ly32) d += (double)v.Ly;
+            if (sa.Lz32) d += (double)v.Lz;
+            if (sa.Lv) d += v.Lv;
+            Uin = v.Uin;
+        }
+        if (finish()) {
+            const double w = Uin + h * d;
+            sa.Uout[o] = sa.a == 0.0 ? sa.b * w : sa.a * v.U0 + sa.b * w;
+        } else {
+            rhs[o] = R(d);
+        }
+    }
+    // all NV fields of one cell, the loads ahead of their uses: all of them at
+    // once, or in the mixed finish, whose values take eight registers a
+    // field, five fields at a time
+    template <int NV, class D, class U>
+    __device__ __forceinline__ void put_all(long long cells, long long cell, D &&d, U &&uin) const {
+        constexpr int B = sizeof(R) == 8 ? NV : 5;
+#pragma unroll
+        for (int b = 0; b < NV; b += B) {
+            Held v[B];
+#pragma unroll
+            for (int k = 0; k < B && b + k < NV; ++k) load((b + k) * cells + cell, v[k]);
+#pragma unroll
+            for (int k = 0; k < B && b + k < NV; ++k)
+                put((b + k) * cells + cell, d(b + k), uin(b + k), v[k]);
+        }
+    }
+};
+
+// Hands the flux components of an exchanging sweep on: the component of this
+// face goes to its own lane's cell (the one below the face) together with the
+// neighbouring face's, taken STEP lanes down; faces in a wave's first and
+// last row leave theirs for the cell between two waves (first, last).
+template <int IM, int STEP, class CO, typename R, class First, class Last, class Uin>
+struct ExchangeOut {
+    const CO &co;
+    long long cells, cell;
+    R id;
+    bool own, top;                   // the cell below is this wave's; the face is in its last row
+    First first;
+    Last last;
+    Uin uin;
+    typename CO::Held held[5];
+    // every lane loads (a cell that is not its own lies in the padded array
+    // too), so that no branch parts the loads from the work ahead of their use
+    __device__ __forceinline__ void start() { co.load(cell, held[0]); }
+    template <int SLOT>
+    __device__ __forceinline__ void next(int q) {
+        co.load(q * cells + cell, held[SLOT]);
+    }
+    __device__ __forceinline__ void rest() {
+#pragma unroll
+        for (int k = 1; k < 4; ++k) co.load((IM + k) * cells + cell, held[1 + k]);
+    }
+    template <int SLOT>
+    __device__ __forceinline__ void put(int q, R v) {
+        const R vb = __shfl_up(v, STEP);       // the face below, valid wherever this face is
+        if (own) {
+            // the FP32 face asks for nothing ahead (its sweeps only store,
+            // but for the y or z sweep that finishes a stage without an x axis)
+            if constexpr (sizeof(R) == 4) co.load(q * cells + cell, held[SLOT]);
+            co.put(q * cells + cell, double((vb - v) * id), uin(q), held[SLOT]);
+        } else {
+            first(q, v);
+        }
+        if (top) last(q, v);
+    }
+};
+
+// Keeps a face's whole flux vector (in LDS).
+template <class Put>
+struct StoreOut {
+    Put f;
+    __device__ __forceinline__ void start() {}
+    template <int SLOT>
+    __device__ __forceinline__ void next(int) {}
+    __device__ __forceinline__ void rest() {}
+    template <int SLOT, typename R>
+    __device__ __forceinline__ void put(int q, R v) {
+        f(q, v);
+    }
+};
+template <class Put>
+__device__ __forceinline__ StoreOut<Put> store_out(Put p) {
+    return StoreOut<Put>{p};
 }
 
 // ---------------------------------------------------------------------------
@@ -332,12 +439,10 @@ inline int x_faces_per_block(long long nfx) {
 // Exchanging x sweeps: FP64 WENO5 (three waves per SIMD).  The CU6 and
 // WENO7 faces (two and one waves per SIMD) took 3.09 ms per x sweep
 // exchanging against 2.62 and 2.65 ms with the fluxes in LDS.
-template <typename R, int REC>
-struct XShape {
-    static constexpr bool exchange = sizeof(R) == 8 && REC == kReconWeno5;
-};
+template <typename R, int REC, bool PP>
+constexpr bool x_exchange() { return sizeof(R) == 8 && REC == kReconWeno5 && !PP; }
 
-template <int NS, typename R, typename S, bool PP, int SPD, int REC>
+template <int NS, typename R, typename S, bool PP, int SPD, int REC, int MODE>
 __global__ __launch_bounds__(kXBlock) __attribute__((amdgpu_waves_per_eu(sweep_waves<R, REC, true, PP>()))) void k_sweep_x(
     const S *__restrict__ U, const S *__restrict__ P, R *__restrict__ rhs, Geo g, ThermoK<R> th, int accumulate,
     StageArgs sa, unsigned *status, Dissip ds, int fpb) {
@@ -345,7 +450,7 @@ __global__ __launch_bounds__(kXBlock) __attribute__((amdgpu_waves_per_eu(sweep_w
     constexpr int RAD = stencil_radius(REC);
     constexpr int GAP = 2 * RAD - 1;
     constexpr int XC = x_stage_cells<RAD>();
-    constexpr bool EXCH = XShape<R, REC>::exchange && !PP;
+    constexpr bool EXCH = x_exchange<R, REC, PP>();
     constexpr int NW = kXBlock / 64;
     __shared__ R sF[EXCH ? 1 : NV][EXCH ? 1 : kXBlock];
     __shared__ R sEdge[2][EXCH ? NW : 1][EXCH ? NV : 1];
@@ -396,73 +501,59 @@ __global__ __launch_bounds__(kXBlock) __attribute__((amdgpu_waves_per_eu(sweep_w
     const long long f = f0 + t;
     const bool valid = t < fpb && f < nfaces;
     const int lane = t & 63, w = t >> 6;
-    int i = 0;
     unsigned flags = 0;
-    long long rowbase = 0;
-    const R id = R(g.idx);
-    // the result of interior cell `cell` from its flux difference L (x part)
-    auto emit = [&](int q, long long cell, double L) {
-        const long long o = q * g.cells + cell;
-        if (sa.Uout) {
-            const double h = sa.dt_dev ? *sa.dt_dev : sa.dt;
-            if constexpr (sizeof(R) == 8) {
-                if (sa.Ly64) L = L + sa.Ly64[o];
-                if (sa.Lz64) L = L + sa.Lz64[o];
-            } else {
-                if (sa.Ly32) L = L + (double)sa.Ly32[o];
-                if (sa.Lz32) L = L + (double)sa.Lz32[o];
-            }
-            if (sa.Lv) L = L + sa.Lv[o];
-            const double v = sa.Uin[o] + h * L;
-            sa.Uout[o] = sa.a == 0.0 ? sa.b * v : sa.a * sa.U0[o] + sa.b * v;
-        } else {
-            put_result(rhs, o, L, accumulate);
-        }
-    };
+    const R id = R(g.idx) * flux_unit<R>();
+    const CellOut<R, MODE> co(rhs, sa, accumulate);
+    const auto *stage = (const __attribute__((address_space(3))) S *)xf_xstage;
+    int e0 = 0;               // staged index of the face's stencil cell 0
+    long long cell = 0;       // the cell below the face
+    bool inner = false;       // and whether it is an interior one
     if (valid) {
-        const int sg = (t + i0) / nfx32;
-        i = t + i0 - sg * nfx32;
-        rowbase = row_base(sg);
+        const int sg = (t + i0) / nfx32, i = t + i0 - sg * nfx32;
+        cell = row_base(sg) + i - 1;
+        inner = i > 0;
         // stencil cell m of face i (cell i - RAD + m of its row) is staged at
         // t + sg GAP + m
-        StencilLds<NV, S> st{(const __attribute__((address_space(3))) S *)xf_xstage, t + sg * GAP, 1, XC};
+        e0 = t + sg * GAP;
+        StencilLds<NV, S> st{stage, e0, 1, XC};
         if constexpr (SPD == kViscFrozen) ds.fidx = f;   // x faces: i + (nx + 1) (j + ny k)
         if constexpr (EXCH) {
-            face_flux_to<NS, R, 0, SweepTune<R>::fence_face, SPD, REC, true, true>(
-                st, th,
-                [&](int q, R v) {
-                    // face f - 1 is lane t - 1, valid wherever face f is
-                    const R vb = __shfl_up(v, 1);
-                    if (lane > 0 && i > 0) emit(q, rowbase + i - 1, double((vb - v) * id));
-                    if (lane == 63) sEdge[0][w][q] = v;
-                    if (lane == 0) sEdge[1][w][q] = v;
-                },
-                flags, ds);
+            auto first = [&](int q, R v) {
+                if (lane == 0) sEdge[1][w][q] = v;
+            };
+            auto last = [&](int q, R v) { sEdge[0][w][q] = v; };
+            auto uin = [&](int q) { return (double)st.u(q, RAD - 1); };
+            // face f - 1 is lane t - 1
+            ExchangeOut<NS, 1, decltype(co), R, decltype(first), decltype(last), decltype(uin)> out{
+                co, g.cells, cell, id, lane > 0 && inner, lane == 63, first, last, uin};
+            sweep_face<NS, R, 0, SPD, REC>(st, th, out, flags, ds);
         } else {
-            face_flux_to<NS, R, 0, SweepTune<R>::fence_face, SPD, REC, !PP, true>(
-                st, th, [&](int q, R v) { sF[q][t] = v; }, flags, ds);
+            auto out = store_out([&](int q, R v) { sF[q][t] = v; });
+            sweep_face<NS, R, 0, SPD, REC>(st, th, out, flags, ds);
             if constexpr (PP) {
                 R Fq[NV];
 #pragma unroll
-                for (int q = 0; q < NV; ++q) Fq[q] = sF[q][t];
+                for (int q = 0; q < NV; ++q) Fq[q] = sF[q][t] * flux_unit<R>();
                 pp_limit<NS, R, 0, RAD>(st, pp_lambda<R>(g, sa, g.idx), Fq);
 #pragma unroll
-                for (int q = 0; q < NV; ++q) sF[q][t] = Fq[q];
+                for (int q = 0; q < NV; ++q) sF[q][t] = Fq[q] * (R(1) / flux_unit<R>());
             }
         }
     }
     __syncthreads();
-    if constexpr (EXCH) {
-        // the cell between the last face of wave w - 1 and the first of w
-        if (valid && lane == 0 && w > 0 && i > 0) {
-#pragma unroll
-            for (int q = 0; q < NV; ++q)
-                emit(q, rowbase + i - 1, double((sEdge[0][w - 1][q] - sEdge[1][w][q]) * id));
-        }
-    } else if (valid && t > 0 && i > 0) {
-#pragma unroll
-        for (int q = 0; q < NV; ++q) emit(q, rowbase + i - 1, double((sF[q][t - 1] - sF[q][t]) * id));
-    }
+    // EXCH: only the cell between the last face of wave w - 1 and the first of
+    // w is left
+    const bool left = EXCH ? lane == 0 && w > 0 : t > 0;
+    if (left && inner)
+        co.template put_all<NV>(
+            g.cells, cell,
+            [&](int q) {
+                if constexpr (EXCH)
+                    return double((sEdge[0][w - 1][q] - sEdge[1][w][q]) * id);
+                else
+                    return double((sF[q][t - 1] - sF[q][t]) * id);
+            },
+            [&](int q) { return (double)stage[q * XC + e0 + RAD - 1]; });
     if (flags) atomicOr(status, flags);
 }
 
@@ -497,7 +588,7 @@ struct TileShape {
     static constexpr int x = exchange ? 8 : 16, s = exchange ? 32 : 16;
 };
 
-template <int NS, typename R, int DIR, typename S, bool PP, int SPD, int REC>
+template <int NS, typename R, int DIR, typename S, bool PP, int SPD, int REC, int MODE>
 __global__ __launch_bounds__((TileShape<R, REC, PP>::x * TileShape<R, REC, PP>::s)) __attribute__((amdgpu_waves_per_eu(sweep_waves<R, REC, false, PP>()))) void
 k_sweep_tile(const S *__restrict__ U, const S *__restrict__ P, R *__restrict__ rhs, Geo g, ThermoK<R> th,
              int accumulate, StageArgs sa, unsigned *status, Dissip ds) {
@@ -505,7 +596,6 @@ k_sweep_tile(const S *__restrict__ U, const S *__restrict__ P, R *__restrict__ r
     using Shape = TileShape<R, REC, PP>;
     constexpr int kTileX = Shape::x, kTileS = Shape::s;
     constexpr int RAD = stencil_radius(REC);
-    constexpr bool STAGE = true;
     constexpr int kRows = kTileS + 2 * RAD - 1;        // stencil rows of the tile's faces
     constexpr int TSZ = kRows * kTileX;                // staged cells
     // EXCH: each flux component goes to the cell below as soon as it is
@@ -519,7 +609,7 @@ k_sweep_tile(const S *__restrict__ U, const S *__restrict__ P, R *__restrict__ r
     constexpr int NWV = kTileS / RPW;                  // waves per block
     __shared__ R sF[EXCH ? 1 : NV][EXCH ? 1 : kTileS][EXCH ? 1 : kTileX];
     __shared__ R sEdge[2][EXCH ? NWV : 1][EXCH ? NV : 1][EXCH ? kTileX : 1];
-    __shared__ S xf_ftile[STAGE ? (NV + 4) * TSZ : 1];
+    __shared__ S xf_ftile[(NV + 4) * TSZ];
     unsigned bx, by, bz;
     xcd_block(bx, by, bz);
     const int tx = threadIdx.x, ts = threadIdx.y;
@@ -533,7 +623,7 @@ k_sweep_tile(const S *__restrict__ U, const S *__restrict__ P, R *__restrict__ r
     const long long plane = (DIR == 1) ? (long long)(g.gz + bz) * g.sz : (long long)(g.gy + bz) * g.sy;
     const long long col = (long long)(g.gx + x) + plane;
     unsigned flags = 0;
-    if constexpr (STAGE) {
+    {
         // tile row r = padded sweep row gs + j0 - RAD + r, for the tile's x
         // columns; rows past the padded extent and columns past the interior
         // are never read
@@ -548,67 +638,53 @@ k_sweep_tile(const S *__restrict__ U, const S *__restrict__ P, R *__restrict__ r
 #pragma unroll
             for (int k = 0; k < 4; ++k) xf_ftile[(NV + k) * TSZ + e] = P[k * g.cells + cell];
         }
-        __syncthreads();
     }
+    __syncthreads();
+    const R id = R((DIR == 1) ? g.idy : g.idz) * flux_unit<R>();
+    const CellOut<R, MODE> co(rhs, sa, accumulate);
+    const long long below = col + (long long)(gs + j - 1) * step;   // the cell below the face
+    const auto *stage = (const __attribute__((address_space(3))) S *)xf_ftile;
+    const int r = ts % RPW, w = ts / RPW;
     if (valid) {
         if constexpr (SPD == kViscFrozen)   // y faces: i + nx (j + (ny + 1) k); z faces: i + nx (j + ny k)
             ds.fidx = DIR == 1 ? x + (long long)g.nx * (j + (long long)(g.ny + 1) * bz)
                                : x + (long long)g.nx * (bz + (long long)g.ny * j);
-        auto face = [&](const auto &st) {
-            if constexpr (EXCH) {
-                const R id = R((DIR == 1) ? g.idy : g.idz);
-                const int r = ts % RPW, w = ts / RPW;
-                const long long below = col + (long long)(gs + j - 1) * step;
-                face_flux_to<NS, R, DIR, SweepTune<R>::fence_face, SPD, REC, !PP, SweepTune<R>::roll_tile>(
-                    st, th,
-                    [&](int q, R v) {
-                        // face j - 1 of this column, valid wherever face j is
-                        const R vb = __shfl_up(v, kTileX);
-                        if (r > 0) put_result(rhs, q * g.cells + below, double((vb - v) * id), accumulate);
-                        if (r == RPW - 1) sEdge[0][w][q][tx] = v;
-                        if (r == 0) sEdge[1][w][q][tx] = v;
-                    },
-                    flags, ds);
-                return;
-            }
-            face_flux_to<NS, R, DIR, SweepTune<R>::fence_face, SPD, REC, !PP, SweepTune<R>::roll_tile>(
-                st, th, [&](int q, R v) { sF[q][ts][tx] = v; }, flags, ds);
+        // stencil cell m of face j is tile row j - j0 + m
+        const StencilLds<NV, S> st{stage, ts * kTileX + tx, kTileX, TSZ};
+        if constexpr (EXCH) {
+            auto first = [&](int q, R v) { sEdge[1][w][q][tx] = v; };
+            auto last = [&](int q, R v) { sEdge[0][w][q][tx] = v; };
+            auto uin = [&](int q) { return (double)st.u(q, RAD - 1); };
+            ExchangeOut<NS, kTileX, decltype(co), R, decltype(first), decltype(last), decltype(uin)> out{
+                co, g.cells, below, id, r > 0, r == RPW - 1, first, last, uin};
+            sweep_face<NS, R, DIR, SPD, REC>(st, th, out, flags, ds);
+        } else {
+            auto out = store_out([&](int q, R v) { sF[q][ts][tx] = v; });
+            sweep_face<NS, R, DIR, SPD, REC>(st, th, out, flags, ds);
             if constexpr (PP) {
                 R Fq[NV];
 #pragma unroll
-                for (int q = 0; q < NV; ++q) Fq[q] = sF[q][ts][tx];
+                for (int q = 0; q < NV; ++q) Fq[q] = sF[q][ts][tx] * flux_unit<R>();
                 pp_limit<NS, R, DIR, RAD>(st, pp_lambda<R>(g, sa, DIR == 1 ? g.idy : g.idz), Fq);
 #pragma unroll
-                for (int q = 0; q < NV; ++q) sF[q][ts][tx] = Fq[q];
+                for (int q = 0; q < NV; ++q) sF[q][ts][tx] = Fq[q] * (R(1) / flux_unit<R>());
             }
-        };
-        if constexpr (STAGE) {
-            // stencil cell m of face j is tile row j - j0 + m
-            face(StencilLds<NV, S>{(const __attribute__((address_space(3))) S *)xf_ftile, ts * kTileX + tx, kTileX,
-                                   TSZ});
-        } else {
-            face(StencilT<S>{U, P, col + (long long)(gs + j - RAD) * step, step, g.cells});
         }
     }
     __syncthreads();
-    if constexpr (EXCH) {
-        // the cell between the last face row of wave w - 1 and the first of w
-        const int r = ts % RPW, w = ts / RPW;
-        if (valid && r == 0 && w > 0) {
-            const R id = R((DIR == 1) ? g.idy : g.idz);
-            const long long cell = col + (long long)(gs + j - 1) * step;
-#pragma unroll
-            for (int q = 0; q < NV; ++q)
-                put_result(rhs, q * g.cells + cell, double((sEdge[0][w - 1][q][tx] - sEdge[1][w][q][tx]) * id),
-                           accumulate);
-        }
-    } else if (valid && ts > 0) {
-        const R id = R((DIR == 1) ? g.idy : g.idz);
-        const long long cell = col + (long long)(gs + j - 1) * step;
-#pragma unroll
-        for (int q = 0; q < NV; ++q)
-            put_result(rhs, q * g.cells + cell, double((sF[q][ts - 1][tx] - sF[q][ts][tx]) * id), accumulate);
-    }
+    // EXCH: only the cell between the last face row of wave w - 1 and the
+    // first of w is left
+    const bool left = EXCH ? r == 0 && w > 0 : ts > 0;
+    if (valid && left)
+        co.template put_all<NV>(
+            g.cells, below,
+            [&](int q) {
+                if constexpr (EXCH)
+                    return double((sEdge[0][w - 1][q][tx] - sEdge[1][w][q][tx]) * id);
+                else
+                    return double((sF[q][ts - 1][tx] - sF[q][ts][tx]) * id);
+            },
+            [&](int q) { return (double)stage[q * TSZ + (ts + RAD - 1) * kTileX + tx]; });
     if (flags) atomicOr(status, flags);
 }
 

@@ -141,13 +141,6 @@ __global__ __launch_bounds__(256) void k_sum_dirs(double *rhs, const float *Lx, 
     rhs[o] = L;
 }
 
-// y = a x + b y (b == 0 ignores the old y, so y may hold anything)
-__global__ __launch_bounds__(256) void k_axpby(long long n, double a, const double *x, double b, double *y) {
-    const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n) return;
-    y[q] = b == 0.0 ? a * x[q] : a * x[q] + b * y[q];
-}
-
 // Adjoint of one stage given the stage cotangent lam (of the stage output)
 // and mu = J(V)^T lam (the rhs-VJP at that stage's input V):
 //   stage 3 (U = 1/3 V0 + 2/3 (V2 + dt L(V2))): lam0 = lam/3;      lam = 2/3 (lam + dt mu)
@@ -270,11 +263,6 @@ hipError_t launch_rk3_stage_vjp(const LaunchCtx &c, int nv, int stage, double *l
 hipError_t launch_sum_dirs(const LaunchCtx &c, int nv, double *rhs, const float *const L[3], hipStream_t s) {
     const long long n = (long long)c.g.nx * c.g.ny * c.g.nz * nv;
     hipLaunchKernelGGL(k_sum_dirs, dim3(blocks_for(n, 256)), dim3(256), 0, s, rhs, L[0], L[1], L[2], c.g, nv);
-    return hipGetLastError();
-}
-
-hipError_t launch_axpy_state(long long n, double a, const double *x, double b, double *y, hipStream_t s) {
-    hipLaunchKernelGGL(k_axpby, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, a, x, b, y);
     return hipGetLastError();
 }
 

@@ -24,7 +24,7 @@ hipError_t prims(const LaunchCtx &c, const double *U, double *P, float *Uf, floa
     return hipGetLastError();
 }
 
-template <typename R, typename S, bool PP, int SPD, int REC>
+template <typename R, typename S, bool PP, int SPD, int REC, int MODE>
 hipError_t launch_face_sweep(const LaunchCtx &c, const ThermoK<R> &th, int dir, int accumulate, const S *U,
                              const S *P, R *rhs, const StageArgs &sa, const Dissip &ds, hipStream_t s) {
     const Geo &g = c.g;
@@ -35,7 +35,9 @@ hipError_t launch_face_sweep(const LaunchCtx &c, const ThermoK<R> &th, int dir, 
         // of the XCD count so that each XCD takes one contiguous range
         unsigned nb = (unsigned)((nf - 1 + (fpb - 2)) / (fpb - 1));
         nb = (nb + kNumXcd - 1) / kNumXcd * kNumXcd;
-        hipLaunchKernelGGL((k_sweep_x<NS, R, S, PP, SPD, REC>), dim3(nb), dim3(kXBlock), 0, s, U, P, rhs, g, th,
+        // the FP32 x sweep keeps its fluxes in LDS: one instance for all modes
+        constexpr int XM = x_exchange<R, REC, PP>() ? MODE : kByArgs;
+        hipLaunchKernelGGL((k_sweep_x<NS, R, S, PP, SPD, REC, XM>), dim3(nb), dim3(kXBlock), 0, s, U, P, rhs, g, th,
                            accumulate, sa, c.status, ds, fpb);
         return hipGetLastError();
     }
@@ -45,12 +47,34 @@ hipError_t launch_face_sweep(const LaunchCtx &c, const ThermoK<R> &th, int dir, 
     const unsigned tiles = (unsigned)((nsw + TS - 2) / (TS - 1));
     dim3 grid((g.nx + TX - 1) / TX, tiles, ntr), block(TX, TS);
     if (dir == 1)
-        hipLaunchKernelGGL((k_sweep_tile<NS, R, 1, S, PP, SPD, REC>), grid, block, 0, s, U, P, rhs, g, th, accumulate,
-                           sa, c.status, ds);
+        hipLaunchKernelGGL((k_sweep_tile<NS, R, 1, S, PP, SPD, REC, MODE>), grid, block, 0, s, U, P, rhs, g, th,
+                           accumulate, sa, c.status, ds);
     else
-        hipLaunchKernelGGL((k_sweep_tile<NS, R, 2, S, PP, SPD, REC>), grid, block, 0, s, U, P, rhs, g, th, accumulate,
-                           sa, c.status, ds);
+        hipLaunchKernelGGL((k_sweep_tile<NS, R, 2, S, PP, SPD, REC, MODE>), grid, block, 0, s, U, P, rhs, g, th,
+                           accumulate, sa, c.status, ds);
     return hipGetLastError();
+}
+
+// The instance for what the sweep does with its differences: the exchanging
+// sweeps have one each, the others read it from their arguments.
+template <typename R, typename S, bool PP, int SPD, int REC>
+hipError_t face_sweep_mode(const LaunchCtx &c, const ThermoK<R> &th, int dir, int accumulate, const S *U, const S *P,
+                           R *rhs, const StageArgs &sa, const Dissip &ds, hipStream_t s) {
+    if constexpr (TileShape<R, REC, PP>::exchange) {
+        if constexpr (SPD != kViscFrozen) {
+            if (sa.Uout)
+                return launch_face_sweep<R, S, PP, SPD, REC, kFinish>(c, th, dir, accumulate, U, P, rhs, sa, ds, s);
+        } else if (sa.Uout) {
+            return hipErrorInvalidValue;   // given speeds: right-hand sides only
+        }
+        if constexpr (sizeof(R) == 8) {    // FP32 differences are never accumulated
+            if (accumulate)
+                return launch_face_sweep<R, S, PP, SPD, REC, kAdd>(c, th, dir, accumulate, U, P, rhs, sa, ds, s);
+        }
+        return launch_face_sweep<R, S, PP, SPD, REC, kStore>(c, th, dir, accumulate, U, P, rhs, sa, ds, s);
+    } else {
+        return launch_face_sweep<R, S, PP, SPD, REC, kByArgs>(c, th, dir, accumulate, U, P, rhs, sa, ds, s);
+    }
 }
 
 // One instance per (positivity blend, artificial viscosity, reconstruction).
@@ -58,10 +82,10 @@ template <typename R, typename S, bool PP, int SPD>
 hipError_t face_sweep_rec(const LaunchCtx &c, const ThermoK<R> &th, int dir, int accumulate, const S *U, const S *P,
                           R *rhs, const StageArgs &sa, const Dissip &ds, hipStream_t s) {
     switch (ds.recon) {
-        case kReconCu6: return launch_face_sweep<R, S, PP, SPD, kReconCu6>(c, th, dir, accumulate, U, P, rhs, sa, ds, s);
+        case kReconCu6: return face_sweep_mode<R, S, PP, SPD, kReconCu6>(c, th, dir, accumulate, U, P, rhs, sa, ds, s);
         case kReconWeno7:
-            return launch_face_sweep<R, S, PP, SPD, kReconWeno7>(c, th, dir, accumulate, U, P, rhs, sa, ds, s);
-        default: return launch_face_sweep<R, S, PP, SPD, kReconWeno5>(c, th, dir, accumulate, U, P, rhs, sa, ds, s);
+            return face_sweep_mode<R, S, PP, SPD, kReconWeno7>(c, th, dir, accumulate, U, P, rhs, sa, ds, s);
+        default: return face_sweep_mode<R, S, PP, SPD, kReconWeno5>(c, th, dir, accumulate, U, P, rhs, sa, ds, s);
     }
 }
 
@@ -110,19 +134,6 @@ hipError_t sweep_frozen(const LaunchCtx &c, int dir, int accumulate, const doubl
         return face_sweep_rec<float, float, false, kViscFrozen>(c, c.th32, dir, 0, Uf, Pf, rhs32, off, ds, s);
     }
     return face_sweep_rec<double, double, false, kViscFrozen>(c, c.th64, dir, accumulate, U, P, rhs, off, ds, s);
-}
-
-hipError_t stage(const LaunchCtx &c, double *Uout, const double *U0, const double *Uin, const double *const L64[3],
-                 const float *const L32[3], const double *Lv, double a, double b, double dt, const double *dt_dev,
-                 hipStream_t s) {
-    const dim3 grid((unsigned)c.g.ny * c.g.nz, NS + 4), block(256);
-    if (c.precision == XF_PREC_MIXED)
-        hipLaunchKernelGGL(k_stage_sum<float>, grid, block, 0, s, Uout, U0, Uin, L32[0], L32[1], L32[2], Lv, c.g, a,
-                           b, dt, dt_dev);
-    else
-        hipLaunchKernelGGL(k_stage_sum<double>, grid, block, 0, s, Uout, U0, Uin, L64[0], L64[1], L64[2], Lv, c.g, a,
-                           b, dt, dt_dev);
-    return hipGetLastError();
 }
 
 hipError_t face_speeds(const LaunchCtx &c, int dir, const double *U, const double *P, const double *glf,
@@ -271,8 +282,7 @@ hipError_t viscous(const LaunchCtx &c, int dir, const double *U, const double *P
     return hipGetLastError();
 }
 
-const NsOps kOps = {prims, sweep, sweep_vjp, sweep_frozen, face_speeds, glf, prims_vjp, cfl, transport, viscous, react_launch<NS>,
-                    stage};
+const NsOps kOps = {prims, sweep, sweep_vjp, sweep_frozen, face_speeds, glf, prims_vjp, cfl, transport, viscous, react_launch<NS>};
 
 }  // namespace
 
