@@ -40,7 +40,7 @@
 // compiler from hoisting every stencil load to the top of the routine (which
 // holds ~100 loaded values in registers at once); emits no instruction.
 #ifdef __HIP_DEVICE_COMPILE__
-#define XF_FENCE() do { asm volatile("" ::: "memory"); __builtin_amdgcn_sched_barrier(0); } while (0)
+#define XF_FENCE() asm volatile("" ::: "memory")
 #else
 #define XF_FENCE() ((void)0)
 #endif

@@ -18,8 +18,11 @@
 //   * sum_s chi_s rho_s = Gamma (q^2/2 rho - sum_s e_s rho_s) + T~ sum_s R_s
 //     rho_s, so the species thermo is evaluated once for the Roe state and
 //     the six cells together, and n.F_m - u_n F_rho = u_n (n.m - u~_n rho) + p.
-// Executed FP64 operations per nine-species face: 2372 -> XX wave
-// instructions.
+// Vector instructions per nine-species face in a y/z tile: 3198 in the plain
+// forms, 2420 with those above, 2128 with the constants and the uniform
+// polynomial coefficients in scalar registers (in_sgpr, fma_uniform) and the
+// exchange's lane index formed once.  z sweep at 256^3, nine species: 1.95 ->
+// 1.60 -> 1.52 ms.
 #pragma once
 
 #include "xf_face.hpp"
@@ -43,6 +46,48 @@ XF_HD double rsqrt_nr(double x) {
     return fma(0.5 * y, e, y);
 }
 
+// A constant held in scalar registers: left to itself the compiler takes most
+// FP64 constants as literals, which only the two-operand multiply-add accepts,
+// and then copies the addend first wherever it is needed again.
+XF_HD double in_sgpr(double v) {
+#ifdef __HIP_DEVICE_COMPILE__
+    asm("" : "+s"(v));
+#endif
+    return v;
+}
+// a * b + c with c uniform, as one instruction (the compiler copies a uniform
+// addend into the destination's registers first)
+XF_HD double fma_uniform(double a, double b, double c) {
+#ifdef __HIP_DEVICE_COMPILE__
+    double d;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+    return d;
+#else
+    return fma(a, b, c);
+#endif
+}
+// e_s(T) and C_v,s(T) of a species the whole wave works on
+XF_HD double e_uniform(const ThermoK<double> &th, int s, double T) {
+    double v = fma(T, th.e[s][5], th.e[s][4]);
+#pragma unroll
+    for (int k = 3; k >= 0; --k) v = fma_uniform(v, T, th.e[s][k]);
+    return v;
+}
+XF_HD double cv_uniform(const ThermoK<double> &th, int s, double T) {
+    double v = fma(T, th.cv[s][4], th.cv[s][3]);
+#pragma unroll
+    for (int k = 2; k >= 0; --k) v = fma_uniform(v, T, th.cv[s][k]);
+    return v;
+}
+
+// Constants of the WENO5 weights.
+struct WenoK {
+    double a, b, h, c3, c5, c6, c12, sixth;
+    XF_HD WenoK()
+        : a(in_sgpr(-1.375)), b(in_sgpr(-0.625)), h(in_sgpr(0.609375)), c3(in_sgpr(3.0)), c5(in_sgpr(5.0)),
+          c6(in_sgpr(6.0)), c12(in_sgpr(12.0)), sixth(in_sgpr(1.0 / 6.0)) {}
+};
+
 // Differences per side, the cells they span, and the fluxes' guard: products
 // of the weights' denominators past kWideProduct (never reached by fluxes at
 // SI scales) are taken after both sides are scaled by powers of two.
@@ -53,17 +98,17 @@ constexpr double kWideProduct = 1e280;
 // WENO5-JS from the first differences d0..d3 of the five point values (centre
 // between d1 and d2): the value is centre + N / (6 D).  eps is 1e-6 * 12/16
 // times the square of the values' scale.
-XF_HD void weno5_diff(const double *d, double eps, double &N, double &D) {
-    const double h1 = fma(0.609375 * d[1], d[1], eps), h2 = fma(0.609375 * d[2], d[2], eps);
-    const double z0 = fma(-1.375, d[1], d[0]), z1 = fma(-0.625, d[2], d[1]), z2 = fma(-1.375, d[2], d[3]);
+XF_HD void weno5_diff(const WenoK &K, const double *d, double eps, double &N, double &D) {
+    const double h1 = fma(K.h * d[1], d[1], eps), h2 = fma(K.h * d[2], d[2], eps);
+    const double z0 = fma(K.a, d[1], d[0]), z1 = fma(K.b, d[2], d[1]), z2 = fma(K.a, d[2], d[3]);
     const double s0 = fma(z0, z0, h1), s1 = fma(z1, z1, h2), s2 = fma(z2, z2, h2);
     const double p0 = s1 * s2, p1 = s0 * s2, p2 = s0 * s1;
     const double w0 = p0 * p0, w1 = p1 * p1, w2 = p2 * p2;
     // candidates minus the centre, times 6 and the linear weights 1, 6, 3
-    const double m = 12.0 * d[2];
-    const double q0 = fma(5.0, d[1], -2.0 * d[0]), q1 = fma(6.0, d[1], m), q2 = fma(-3.0, d[3], m);
+    const double m = K.c12 * d[2];
+    const double q0 = fma(K.c5, d[1], -2.0 * d[0]), q1 = fma(K.c6, d[1], m), q2 = fma(-K.c3, d[3], m);
     N = fma(w2, q2, fma(w1, q1, w0 * q0));
-    D = fma(3.0, w2, fma(6.0, w1, w0));
+    D = fma(K.c3, w2, fma(K.c6, w1, w0));
 }
 
 // WENO-CU6 from d0..d4 (forms of weno_cu6; the indicators times 12/16):
@@ -132,21 +177,21 @@ XF_HD double weno7_diff(const double *d, double eps) {
 
 // Both sides of one characteristic field, from the centre values cp, cm (g+
 // of cell i, g- of cell i+1) and the differences p (along g+) and m (along
-// the mirrored g-); K the scale of the values.  One reciprocal for the two.
-template <int REC, int K>
-XF_HD double recon_sum(double cp, const double *p, double cm, const double *m) {
+// the mirrored g-); SCALE that of the values.  One reciprocal for the two.
+template <int REC, int SCALE>
+XF_HD double recon_sum(const WenoK &K, double cp, const double *p, double cm, const double *m) {
     if constexpr (REC == kReconWeno7) {
-        constexpr double eps = 1e-6 * (K * K);
+        constexpr double eps = 1e-6 * (SCALE * SCALE);
         return (cp + cm) + (weno7_diff(p, eps) + weno7_diff(m, eps));
     } else {
-        constexpr double eps = 0.75e-6 * (K * K);
+        constexpr double eps = 0.75e-6 * (SCALE * SCALE);
         double Np, Dp, Nm, Dm;
         if constexpr (REC == kReconCu6) {
             cu6_diff(p, eps, Np, Dp);
             cu6_diff(m, eps, Nm, Dm);
         } else {
-            weno5_diff(p, eps, Np, Dp);
-            weno5_diff(m, eps, Nm, Dm);
+            weno5_diff(K, p, eps, Np, Dp);
+            weno5_diff(K, m, eps, Nm, Dm);
         }
         double P = Dp * Dm;
         if (!(P < kWideProduct)) {
@@ -159,7 +204,7 @@ XF_HD double recon_sum(double cp, const double *p, double cm, const double *m) {
             Dm = ldexp(Dm, -em);
             P = Dp * Dm;
         }
-        return fma(fma(Nm, Dp, Np * Dm) * rcp_nr(P), 1.0 / 6.0, cp + cm);
+        return fma(fma(Nm, Dp, Np * Dm) * rcp_nr(P), K.sixth, cp + cm);
     }
 }
 
@@ -185,6 +230,7 @@ XF_HD void face_flux_f64(const St &st, const ThermoK<double> &th, Out &&out, uns
     constexpr int I1 = NS + Axes<DIR>::t1;
     constexpr int I2 = NS + Axes<DIR>::t2;
 
+    const WenoK K;
     // ---- Roe weights, averaged velocity, enthalpy and temperature ---------
     // sqrt(rho_L) / (sqrt(rho_L) + sqrt(rho_R)) from the cells' 1 / rho
     const double iL = st.p(3, CL), iR = st.p(3, CR);
@@ -203,7 +249,7 @@ XF_HD void face_flux_f64(const St &st, const ThermoK<double> &th, Out &&out, uns
     for (int m = 0; m < W; ++m) rh[m] = Se[m] = SR[m] = 0.0;
 #pragma unroll 1
     for (int s = 0; s < NS; ++s) {
-        const double es = e_species(th, s, Tt), cs = cv_species(th, s, Tt), Rs = th.Rs[s];
+        const double es = e_uniform(th, s, Tt), cs = cv_uniform(th, s, Tt), Rs = th.Rs[s];
 #pragma unroll
         for (int m = 0; m < W; ++m) {
             const double r = st.u(s, m);
@@ -288,7 +334,7 @@ XF_HD void face_flux_f64(const St &st, const ThermoK<double> &th, Out &&out, uns
             g = gn;
             if (k + 1 == CL) cm = g;
         }
-        return recon_sum<REC, decltype(scale)::value>(cp, p, cm, m);
+        return recon_sum<REC, decltype(scale)::value>(K, cp, p, cm, m);
     };
     using Two = std::integral_constant<int, 2>;
     using Four = std::integral_constant<int, 4>;
@@ -369,7 +415,7 @@ XF_HD void face_flux_f64(const St &st, const ThermoK<double> &th, Out &&out, uns
         for (int m = 0; m < W; ++m) r[m] = st.u(s, m);
         const double Ys = aL * r[CL] + aR * r[CR];
         // (q^2 - chi_s / Gamma) - q^2 / 2
-        const double ts = fma(-KT, th.Rs[s], e_species(th, s, Tt));
+        const double ts = fma(-KT, th.Rs[s], e_uniform(th, s, Tt));
         double p[ND], m[ND], cp = 0.0, cm = 0.0;
         double tp = r[0] * lp[0], tm = r[W - 1] * lm[0];
 #pragma unroll
@@ -384,7 +430,7 @@ XF_HD void face_flux_f64(const St &st, const ThermoK<double> &th, Out &&out, uns
                 cm = fma(-Ys, DMc, tm);
             }
         }
-        const double hs = recon_sum<REC, 2>(cp, p, cm, m);
+        const double hs = recon_sum<REC, 2>(K, cp, p, cm, m);
         out.template put<SLOT>(s, Ys * Asum + hs);
         gsum += hs;
         gE = fma(ts, hs, gE);

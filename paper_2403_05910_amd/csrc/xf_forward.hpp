@@ -357,6 +357,16 @@ struct ExchangeOut {
     Last last;
     Uin uin;
     typename CO::Held held[5];
+    int from = 4 * (int)((threadIdx.x + blockDim.x * threadIdx.y - STEP) & 63);   // byte index of that lane
+    __device__ __forceinline__ R lanes_down(R v) const {
+        if constexpr (sizeof(R) == 8) {
+            const int lo = __builtin_amdgcn_ds_bpermute(from, __double2loint(v));
+            const int hi = __builtin_amdgcn_ds_bpermute(from, __double2hiint(v));
+            return __hiloint2double(hi, lo);
+        } else {
+            return __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(v)));
+        }
+    }
     // every lane loads (a cell that is not its own lies in the padded array
     // too), so that no branch parts the loads from the work ahead of their use
     __device__ __forceinline__ void start() { co.load(cell, held[0]); }
@@ -370,7 +380,7 @@ struct ExchangeOut {
     }
     template <int SLOT>
     __device__ __forceinline__ void put(int q, R v) {
-        const R vb = __shfl_up(v, STEP);       // the face below, valid wherever this face is
+        const R vb = lanes_down(v);            // the face below, valid wherever this face is
         if (own) {
             // the FP32 face asks for nothing ahead (its sweeps only store,
             // but for the y or z sweep that finishes a stage without an x axis)
@@ -442,6 +452,35 @@ inline int x_faces_per_block(long long nfx) {
 template <typename R, int REC, bool PP>
 constexpr bool x_exchange() { return sizeof(R) == 8 && REC == kReconWeno5 && !PP; }
 
+// Copies U and the primitives of a block's stencil cells into LDS, SZ cells
+// field by field; at(e, cell) tells whether staged cell e exists and gives
+// its padded index.  A block has a few more cells than threads, so some
+// threads take a second one; all loads go out before the first is waited for
+// (one cell at a time, the second waited out a memory latency of its own
+// while most of the block idled).
+template <int NV, int THREADS, int SZ, typename S, class At>
+__device__ __forceinline__ void stage_cells(const S *__restrict__ U, const S *__restrict__ P, long long cells, S *to,
+                                            int t, const At &at) {
+    static_assert(SZ <= 2 * THREADS, "two cells a thread");
+    S a[NV + 4], b[NV + 4];
+    long long ca, cb;
+    const bool ha = at(t, ca), hb = t + THREADS < SZ && at(t + THREADS, cb);
+    auto load = [&](S *v, long long cell) {
+#pragma unroll
+        for (int q = 0; q < NV; ++q) v[q] = U[q * cells + cell];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[NV + q] = P[q * cells + cell];
+    };
+    auto store = [&](const S *v, int e) {
+#pragma unroll
+        for (int q = 0; q < NV + 4; ++q) to[q * SZ + e] = v[q];
+    };
+    if (ha) load(a, ca);
+    if (hb) load(b, cb);
+    if (ha) store(a, t);
+    if (hb) store(b, t + THREADS);
+}
+
 template <int NS, typename R, typename S, bool PP, int SPD, int REC, int MODE>
 __global__ __launch_bounds__(kXBlock) __attribute__((amdgpu_waves_per_eu(sweep_waves<R, REC, true, PP>()))) void k_sweep_x(
     const S *__restrict__ U, const S *__restrict__ P, R *__restrict__ rhs, Geo g, ThermoK<R> th, int accumulate,
@@ -487,15 +526,12 @@ __global__ __launch_bounds__(kXBlock) __attribute__((amdgpu_waves_per_eu(sweep_w
         const int nseg = (int)(flast / nfx - row0) + 1;
         const int ncell = (int)(flast - f0 + 1) + nseg * GAP;
         const int W = nfx32 + GAP;
-        for (int e = t; e < ncell; e += kXBlock) {
+        auto at = [&](int e, long long &cell) {
             const int sg = (e + i0) / W;
-            const int cx = e + i0 - sg * W - RAD;
-            const long long cell = row_base(sg) + cx;
-#pragma unroll
-            for (int q = 0; q < NV; ++q) xf_xstage[q * XC + e] = U[q * g.cells + cell];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) xf_xstage[(NV + q) * XC + e] = P[q * g.cells + cell];
-        }
+            cell = row_base(sg) + (e + i0 - sg * W - RAD);
+            return e < ncell;
+        };
+        stage_cells<NV, kXBlock, XC>(U, P, g.cells, xf_xstage, t, at);
     }
     __syncthreads();
     const long long f = f0 + t;
@@ -628,16 +664,12 @@ k_sweep_tile(const S *__restrict__ U, const S *__restrict__ P, R *__restrict__ r
         // columns; rows past the padded extent and columns past the interior
         // are never read
         const int npad = nsw + 2 * gs;
-        for (int e = ts * kTileX + tx; e < TSZ; e += kTileX * kTileS) {
-            const int r = e / kTileX, cx = bx * kTileX + (e % kTileX);
-            const int row = gs + j0 - RAD + r;
-            if (cx >= g.nx || row >= npad) continue;
-            const long long cell = plane + g.gx + cx + (long long)row * step;
-#pragma unroll
-            for (int q = 0; q < NV; ++q) xf_ftile[q * TSZ + e] = U[q * g.cells + cell];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) xf_ftile[(NV + k) * TSZ + e] = P[k * g.cells + cell];
-        }
+        auto at = [&](int e, long long &cell) {
+            const int cx = bx * kTileX + (e % kTileX), row = gs + j0 - RAD + e / kTileX;
+            cell = plane + g.gx + cx + (long long)row * step;
+            return e < TSZ && cx < g.nx && row < npad;
+        };
+        stage_cells<NV, kTileX * kTileS, TSZ>(U, P, g.cells, xf_ftile, ts * kTileX + tx, at);
     }
     __syncthreads();
     const R id = R((DIR == 1) ? g.idy : g.idz) * flux_unit<R>();
