@@ -323,10 +323,11 @@ int stage_into(xf_ctx *c, const double *in, double *out, const double *U0, doubl
     const bool mixed = lc.precision == XF_PREC_MIXED;
     const int last = n[0] > 1 ? 0 : n[1] > 1 ? 1 : 2;
     bool any = false;   // L holds something
+    const bool apart = mixed && c->ops->few32_stage && (c->viscous || c->pp || last != 0);
     for (int d = 2; d >= last; --d) {
         if (n[d] <= 1) continue;
         xf::StageArgs sw{dt, h_dev, c->pp};
-        if (d == last) {
+        if (d == last && !apart) {
             if (c->viscous) {
                 double *to = mixed ? Lv : L;
                 if (mixed || !any)
@@ -352,6 +353,16 @@ int stage_into(xf_ctx *c, const double *in, double *out, const double *U0, doubl
                                  sw, glf_of(c, pb.mx, d), s);
         }));
         any = true;
+    }
+    if (apart) {
+        const float *const Ld[3] = {n[0] > 1 ? pb.lf(0) : nullptr, n[1] > 1 ? pb.lf(1) : nullptr,
+                                    n[2] > 1 ? pb.lf(2) : nullptr};
+        if (Lv) XF_TRY(timed(c, XF_K_ZERO, s, [&] { return xf::launch_zero(lc.g.cells * c->nv, Lv, s); }));
+        double *const vout[3] = {Lv, Lv, Lv};
+        const int r = viscous_into(c, in, pb, vout, s);
+        if (r != XF_OK) return r;
+        XF_TRY(timed(c, XF_K_STAGE, s,
+                     [&] { return c->ops->few32_stage(lc, out, U0, in, Ld, Lv, a, b, dt, h_dev, s); }));
     }
     return XF_OK;
 }

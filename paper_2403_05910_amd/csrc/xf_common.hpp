@@ -185,6 +185,14 @@ struct NsOps {
     // sub-steps over scale * (dt_dev ? *dt_dev : dt)
     hipError_t (*react)(const LaunchCtx &, double *U, const ReactK *rk, double dt, const double *dt_dev,
                         double scale, int n_sub, hipStream_t);
+    // set in mixed contexts of one and two species, whose sweeps leave all
+    // stages but those of a plain x sweep to it: the SSP-RK3 stage on the
+    // interior, Uout = a U0 + b (Uin + h (((Lx + Ly) + Lz) + Lv)), h = dt_dev ?
+    // *dt_dev : dt, a == 0 skipping U0; L[d] null for an inactive direction,
+    // Lv may be null, Uout may alias U0
+    hipError_t (*few32_stage)(const LaunchCtx &, double *Uout, const double *U0, const double *Uin,
+                              const float *const L[3], const double *Lv, double a, double b, double dt,
+                              const double *dt_dev, hipStream_t);
 };
 
 // The reaction launcher of one species count, from its own translation unit

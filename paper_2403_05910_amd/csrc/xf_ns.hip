@@ -1,7 +1,7 @@
 // xf_ns.hip -- launchers of the species-templated kernels for one species
 // count.  Compiled once per N with -DXF_NS=N; each object exports
 // xf::ops_ns<N>(), which the C ABI collects into its dispatch table.
-#include "xf_forward.hpp"
+#include "xf_few32.hpp"
 #include "xf_viscous.hpp"
 #include "xf_vjp.hpp"
 
@@ -37,8 +37,12 @@ hipError_t launch_face_sweep(const LaunchCtx &c, const ThermoK<R> &th, int dir, 
         nb = (nb + kNumXcd - 1) / kNumXcd * kNumXcd;
         // the FP32 x sweep keeps its fluxes in LDS: one instance for all modes
         constexpr int XM = x_exchange<R, REC, PP>() ? MODE : kByArgs;
-        hipLaunchKernelGGL((k_sweep_x<NS, R, S, PP, SPD, REC, XM>), dim3(nb), dim3(kXBlock), 0, s, U, P, rhs, g, th,
-                           accumulate, sa, c.status, ds, fpb);
+        if constexpr (few32<NS, R>())
+            hipLaunchKernelGGL((k_few32_x<NS, PP, SPD, REC>), dim3(nb), dim3(kXBlock), 0, s, U, P, rhs, g, th, accumulate,
+                               sa, c.status, ds, fpb);
+        else
+            hipLaunchKernelGGL((k_sweep_x<NS, R, S, PP, SPD, REC, XM>), dim3(nb), dim3(kXBlock), 0, s, U, P, rhs, g, th,
+                               accumulate, sa, c.status, ds, fpb);
         return hipGetLastError();
     }
     const int ntr = dir == 1 ? g.nz : g.ny;
@@ -46,12 +50,19 @@ hipError_t launch_face_sweep(const LaunchCtx &c, const ThermoK<R> &th, int dir, 
     constexpr int TX = TileShape<R, REC, PP>::x, TS = TileShape<R, REC, PP>::s;
     const unsigned tiles = (unsigned)((nsw + TS - 2) / (TS - 1));
     dim3 grid((g.nx + TX - 1) / TX, tiles, ntr), block(TX, TS);
+    auto tile = [&](auto d) {
+        constexpr int DIR = decltype(d)::value;
+        if constexpr (few32<NS, R>())
+            hipLaunchKernelGGL((k_few32_tile<NS, DIR, PP, SPD, REC>), grid, block, 0, s, U, P, rhs, g, th, accumulate, sa,
+                               c.status, ds);
+        else
+            hipLaunchKernelGGL((k_sweep_tile<NS, R, DIR, S, PP, SPD, REC, MODE>), grid, block, 0, s, U, P, rhs, g, th,
+                               accumulate, sa, c.status, ds);
+    };
     if (dir == 1)
-        hipLaunchKernelGGL((k_sweep_tile<NS, R, 1, S, PP, SPD, REC, MODE>), grid, block, 0, s, U, P, rhs, g, th,
-                           accumulate, sa, c.status, ds);
+        tile(std::integral_constant<int, 1>{});
     else
-        hipLaunchKernelGGL((k_sweep_tile<NS, R, 2, S, PP, SPD, REC, MODE>), grid, block, 0, s, U, P, rhs, g, th,
-                           accumulate, sa, c.status, ds);
+        tile(std::integral_constant<int, 2>{});
     return hipGetLastError();
 }
 
@@ -60,7 +71,11 @@ hipError_t launch_face_sweep(const LaunchCtx &c, const ThermoK<R> &th, int dir, 
 template <typename R, typename S, bool PP, int SPD, int REC>
 hipError_t face_sweep_mode(const LaunchCtx &c, const ThermoK<R> &th, int dir, int accumulate, const S *U, const S *P,
                            R *rhs, const StageArgs &sa, const Dissip &ds, hipStream_t s) {
-    if constexpr (TileShape<R, REC, PP>::exchange) {
+    if constexpr (few32<NS, R>()) {
+        // only the x sweep finishes a stage here
+        if (sa.Uout && dir != 0) return hipErrorInvalidValue;
+        return launch_face_sweep<R, S, PP, SPD, REC, kByArgs>(c, th, dir, accumulate, U, P, rhs, sa, ds, s);
+    } else if constexpr (TileShape<R, REC, PP>::exchange) {
         if constexpr (SPD != kViscFrozen) {
             if (sa.Uout)
                 return launch_face_sweep<R, S, PP, SPD, REC, kFinish>(c, th, dir, accumulate, U, P, rhs, sa, ds, s);
@@ -136,6 +151,17 @@ hipError_t sweep_frozen(const LaunchCtx &c, int dir, int accumulate, const doubl
     return face_sweep_rec<double, double, false, kViscFrozen>(c, c.th64, dir, accumulate, U, P, rhs, off, ds, s);
 }
 
+hipError_t few32_stage(const LaunchCtx &c, double *Uout, const double *U0, const double *Uin, const float *const L[3],
+                       const double *Lv, double a, double b, double dt, const double *dt_dev, hipStream_t s) {
+    if constexpr (few32<NS, float>()) {
+        const dim3 grid((unsigned)c.g.ny * c.g.nz, NS + 4), block(256);
+        hipLaunchKernelGGL(k_few32_stage<NS>, grid, block, 0, s, Uout, U0, Uin, L[0], L[1], L[2], Lv, c.g, a, b, dt, dt_dev);
+        return hipGetLastError();
+    } else {
+        return hipErrorInvalidValue;
+    }
+}
+
 hipError_t face_speeds(const LaunchCtx &c, int dir, const double *U, const double *P, const double *glf,
                        double *alpha, long long astride, hipStream_t s) {
     if (c.visc == kViscGlf && !glf) return hipErrorInvalidValue;
@@ -173,18 +199,18 @@ hipError_t launch_vjp_group(const LaunchCtx &c, const ThermoK<R> &th, int dir, i
         const int bounds = (63 + rowf - 1) / rowf;               // row boundaries 64 faces can cross
         const int W = 69 + 5 * bounds;
         const size_t per_wave = vjp_x_lds_per_wave<NS, R>(W);
-        // FP64: one wave per block, so the waves of a CU (one per SIMD) run
-        // their staging, faces and window merge out of step (12.3 -> 12.0 ms
-        // per direction at 256^3, nine species, against four-wave blocks)
-        const int wpb = sizeof(R) == 8 ? 1 : (per_wave * 4 <= kVjpLdsBytes ? 4 : 1);
-        if (per_wave * wpb > kVjpLdsBytes) return hipErrorInvalidValue;
+        // one wave per block, so the waves of a CU run their staging, faces
+        // and window merge out of step (FP64, with the plain face, 12.3 ->
+        // 12.0 ms per direction at 256^3, nine species, against four-wave
+        // blocks)
+        if (per_wave > kVjpLdsBytes) return hipErrorInvalidValue;
         const long long waves = (vjp_x_waves_per_plane(g) - grp + kVjpGroups - 1) / kVjpGroups;
-        dim3 grid((unsigned)((waves + wpb - 1) / wpb), g.nz), block(64 * wpb);
+        dim3 grid((unsigned)waves, g.nz), block(64);
         // dynamic LDS above 64 KB must be allowed for the kernel
         const hipError_t e = hipFuncSetAttribute((const void *)k_face_vjp_x<NS, R, CU6>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kVjpLdsBytes);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_face_vjp_x<NS, R, CU6>), grid, block, per_wave * wpb, s, U, P, rbar, Ubar, Pbar, g, th,
+        hipLaunchKernelGGL((k_face_vjp_x<NS, R, CU6>), grid, block, per_wave, s, U, P, rbar, Ubar, Pbar, g, th,
                            W, grp, ds);
     } else {
         const int nsw = dir == 1 ? g.ny : g.nz;
@@ -282,7 +308,8 @@ hipError_t viscous(const LaunchCtx &c, int dir, const double *U, const double *P
     return hipGetLastError();
 }
 
-const NsOps kOps = {prims, sweep, sweep_vjp, sweep_frozen, face_speeds, glf, prims_vjp, cfl, transport, viscous, react_launch<NS>};
+const NsOps kOps = {prims, sweep, sweep_vjp, sweep_frozen, face_speeds, glf, prims_vjp, cfl, transport, viscous, react_launch<NS>,
+                    few32<NS, float>() ? few32_stage : nullptr};
 
 }  // namespace
 
