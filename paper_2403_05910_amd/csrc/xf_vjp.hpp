@@ -186,32 +186,92 @@ XF_HD R dcv_species(const ThermoK<R> &th, int s, R T) {
 // the cell's pressure, of its temperature and of its density rho = sum_s
 // rho_s (added to every partial density by k_prims_vjp).  Lanes of a wave
 // share window cells through different (field, cell) calls, so the
-// read-modify-writes must stay in program order even where one thread's
-// addresses differ: the accesses are volatile (LDS executes a wave's
-// instructions in order).  The pointer carries the LDS address space, so no
-// generic-address checks are generated.
+// additions must stay in program order even where one thread's addresses
+// differ.  The FP64 face uses the LDS's own add, which returns nothing to wait
+// for (LDS executes a wave's instructions in order, so the sums keep a fixed
+// order); the FP32 face reads, adds and writes through volatile accesses,
+// because with the other form the compiler pairs its multiply-adds
+// differently and FP32 results move in the eighth digit.  The pointer carries
+// the LDS address space, so no generic-address checks are generated.
 constexpr int kSinkP = 0, kSinkT = 1, kSinkRho = 2, kSinkExtra = 3;
+template <typename R>
 struct SinkLds {
-    volatile lds_double *w;
+    lds_double *w;
     int W, off, mstep, pofs;   // window length, offset of stencil cell 0, cell stride, start of the extra rows
-    XF_HD void u(int f, int m, double v) const { w[f * W + off + m * mstep] += v; }
-    XF_HD void p(int k, int m, double v) const { w[pofs + k * W + off + m * mstep] += v; }
+    __device__ __forceinline__ void u(int f, int m, double v) const { add(f * W + off + m * mstep, v); }
+    __device__ __forceinline__ void p(int k, int m, double v) const { add(pofs + k * W + off + m * mstep, v); }
+    __device__ __forceinline__ void add(int i, double v) const {
+        if constexpr (sizeof(R) == 8) {
+            (void)__builtin_amdgcn_ds_atomic_fadd_f64(w + i, v);
+        } else {
+            volatile lds_double *o = w + i;
+            *o += v;
+        }
+    }
 };
 
 // Cotangent of the face flux, (rbar_R - rbar_L) / dx of the residual's
-// cotangent at the face's two cells (zero outside the interior); read from
-// memory where it is used.
-struct FaceBar {
+// cotangent at the face's two cells (zero outside the interior): formed once
+// per face, all loads together with the staging's, and kept in LDS, one slot
+// per lane and component (the components are used in loops, out of order and
+// some of them twice; read from memory where used, each use waited out a
+// memory latency).
+template <int NV>
+struct FaceBarLoad {
+    double r[NV], l[NV];
+    __device__ __forceinline__ void load(const double *__restrict__ rbar, long long C, long long cr, long long cl, bool hr,
+                                         bool hl) {
+#pragma unroll
+        for (int q = 0; q < NV; ++q) r[q] = l[q] = 0.0;
+        if (hr) {
+#pragma unroll
+            for (int q = 0; q < NV; ++q) r[q] = rbar[q * C + cr];
+        }
+        if (hl) {
+#pragma unroll
+            for (int q = 0; q < NV; ++q) l[q] = rbar[q * C + cl];
+        }
+    }
+    // into t[q * 64 + lane]; returns whether any component is nonzero
+    template <typename R>
+    __device__ __forceinline__ bool keep(R *t, int lane, double id) const {
+        bool any = false;
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+            const double d = (r[q] - l[q]) * id;
+            any |= d != 0.0;
+            t[q * 64 + lane] = R(d);
+        }
+        return any;
+    }
+};
+// The same read from memory where it is used, and the stencil with it: the
+// FP32 face of a single species, whose loops the compiler takes apart and
+// rounds differently in other surroundings (see xf_few32.hpp).
+template <int NS, typename R>
+constexpr bool vjp_from_memory() { return sizeof(R) == 4 && NS == 1; }
+struct FaceBarMem {
     const double *__restrict__ rbar;
     long long C, cr, cl;   // field stride, right and left cell
     bool hr, hl;           // the right / left cell is interior
     double id;             // 1 / dx of the direction
-    XF_HD double operator()(int q) const {
+    __device__ __forceinline__ double operator()(int q) const {
         const double r = hr ? rbar[q * C + cr] : 0.0;
         const double l = hl ? rbar[q * C + cl] : 0.0;
         return (r - l) * id;
     }
 };
+template <typename R>
+struct FaceBar {
+    const __attribute__((address_space(3))) R *t;   // the lane's slot of component 0
+    __device__ __forceinline__ R operator()(int q) const { return t[q * 64]; }
+};
+
+}  // namespace xf
+
+#include "xf_vjp64.hpp"   // the FP64 face, on the pieces above
+
+namespace xf {
 
 // Forward Roe state of one face (the dissipation speeds of the ROE scheme).
 template <int NS, typename R>
@@ -268,7 +328,7 @@ struct RoeFwd {
 // Gamma u.v_m + Gamma v_E; XU = n.m - u_n rho, XF = n.F_m - u_n F_rho
 // (acoustic rows l_-+ . v = DU/2 -+ c XU/(2 c^2), likewise for F).
 template <int NS, typename R, int DIR, bool CU6, class St, class Bar, class Out>
-XF_HD void face_vjp(St st, const ThermoK<R> &th, const Bar &Fb, const Out &out, const Dissip &ds) {
+__device__ __forceinline__ void face_vjp(St st, const ThermoK<R> &th, const Bar &Fb, const Out &out, const Dissip &ds) {
     constexpr int IM = NS;
     constexpr int IE = NS + 3;
     constexpr int KN = Axes<DIR>::n, K1 = Axes<DIR>::t1, K2 = Axes<DIR>::t2;
@@ -624,17 +684,56 @@ XF_HD void face_vjp(St st, const ThermoK<R> &th, const Bar &Fb, const Out &out, 
     out.p(kSinkRho, 3, double(rR_b - r3 * r3 * r3_b));
 }
 
+// The face VJP in its arithmetic type.
+template <int NS, typename R, int DIR, bool CU6, class St, class Bar>
+__device__ __forceinline__ void vjp_face(const St &st, const ThermoK<R> &th, const Bar &Fb, const SinkLds<R> &out,
+                                         const Dissip &ds) {
+    if constexpr (sizeof(R) == 8)
+        face_vjp_f64<NS, DIR, CU6>(st, th, Fb, out, ds);
+    else
+        face_vjp<NS, R, DIR, CU6>(st, th, Fb, out, ds);
+}
+
 // Waves per SIMD the face VJP kernels are compiled for: the FP32 face keeps
 // its state in 256 registers (two waves); the FP64 one needs up to 512 (one
-// wave; at two it spills 744 bytes per lane).  At one wave per SIMD a block
-// has its CU's LDS to itself, so the FP64 kernels first copy the stencil
-// values of all their faces (U and the primitives) into LDS, and the face
-// computation waits on no global load; the FP32 kernels, two blocks per CU,
-// read the stencil through the caches.
+// wave; at two it spills 744 bytes per lane).  Every block first copies the
+// stencil values of all its faces (U and the primitives, in the face's type)
+// and the face cotangents into LDS, so the face computation waits on no
+// global load.
 template <typename R>
 constexpr int vjp_waves() { return sizeof(R) == 4 ? 2 : 1; }
-template <typename R>
-constexpr bool vjp_staged() { return sizeof(R) == 8; }
+
+// The U and primitives of one cell.
+template <int NV>
+__device__ __forceinline__ void vjp_load(const double *__restrict__ U, const double *__restrict__ P, long long C,
+                                         long long cell, double *v) {
+#pragma unroll
+    for (int q = 0; q < NV; ++q) v[q] = U[q * C + cell];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[NV + k] = P[k * C + cell];
+}
+
+// Ubar, Pbar += the window's value of one cell, all loads ahead of the first
+// store: one field after the other, each load waited behind the store of the
+// field before (the compiler cannot tell them apart), sixteen memory
+// latencies a cell where this takes one.
+template <int NV>
+struct VjpMerge {
+    double v[NV + kSinkExtra];
+    __device__ __forceinline__ void load(const double *Ubar, const double *Pbar, long long C, long long cell) {
+#pragma unroll
+        for (int q = 0; q < NV; ++q) v[q] = Ubar[q * C + cell];
+#pragma unroll
+        for (int k = 0; k < kSinkExtra; ++k) v[NV + k] = Pbar[k * C + cell];
+    }
+    template <class F>
+    __device__ __forceinline__ void store(double *Ubar, double *Pbar, long long C, long long cell, F &&f) const {
+#pragma unroll
+        for (int q = 0; q < NV; ++q) Ubar[q * C + cell] = v[q] + f(q);
+#pragma unroll
+        for (int k = 0; k < kSinkExtra; ++k) Pbar[k * C + cell] = v[NV + k] + f(NV + k);
+    }
+};
 
 // ---------------------------------------------------------------------------
 // The face VJP runs as one kernel per launch group of faces.
@@ -650,16 +749,23 @@ constexpr bool vjp_staged() { return sizeof(R) == 8; }
 // needed.  The window is then added to Ubar / Pbar with coalesced
 // read-modify-writes.  Runs of waves w and w + 1 can share up to five cells,
 // those of w and w + 2 cannot; launch `grp` takes the waves w = grp mod 2.
-// Staged (FP64): the wave first copies the run's U and primitives into a
-// second private LDS area of (NV + 4) W values.
+// The run's U and primitives and the faces' cotangents go to private LDS
+// areas behind the window, of (NV + 4) W and 64 NV values.
 // ---------------------------------------------------------------------------
+// LDS bytes per wave of k_face_vjp_x for a run of W cells.
+template <int NS, typename R>
+constexpr size_t vjp_x_lds_per_wave(int W) {
+    constexpr size_t NV = NS + 4;
+    return ((NV + kSinkExtra) * W * sizeof(double) + ((NV + 4) * W + NV * 64) * sizeof(R) + 15) / 16 * 16;
+}
+
 template <int NS, typename R, bool CU6>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(vjp_waves<R>()))) void k_face_vjp_x(
     const double *__restrict__ U, const double *__restrict__ P, const double *__restrict__ rbar,
     double *__restrict__ Ubar, double *__restrict__ Pbar, Geo g, ThermoK<R> th, int W, int grp, Dissip ds) {
     constexpr int NV = NS + 4;
     constexpr int NW = NV + kSinkExtra;                    // window rows
-    constexpr int NT = vjp_staged<R>() ? NV + 4 : 0;       // staged rows
+    constexpr int NT = NV + 4;                             // staged rows
     extern __shared__ double xf_win[];
     const int wpb = blockDim.x >> 6, wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const long long rowf = (long long)g.nx + 1;          // faces per row
@@ -668,8 +774,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(vjp_waves<R
     const long long wid = kVjpGroups * ((long long)blockIdx.x * wpb + wv) + grp;
     const long long C = g.cells;
     const long long zb = (long long)(g.gz + blockIdx.y) * g.sz + (long long)g.gy * g.sy;   // plane's first row
-    double *w = xf_win + (size_t)wv * (NW + NT) * W;
-    double *tile = w + (size_t)NW * W;
+    double *w = xf_win + (size_t)wv * (vjp_x_lds_per_wave<NS, R>(W) / sizeof(double));
+    R *tile = (R *)(w + (size_t)NW * W);
+    R *bars = tile + (size_t)NT * W;
     const long long f0 = wid * 64, f = f0 + lane;
     const long long r0 = f0 / rowf;
     const long long base0 = zb + r0 * g.sy + (f0 - r0 * rowf);   // stencil cell 0 of the wave's first face
@@ -680,48 +787,48 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(vjp_waves<R
         span = (int)(zb + rl * g.sy + (fl - rl * rowf) - base0) + 6;
     }
     for (int i = lane; i < NW * W; i += 64) w[i] = 0.0;
-    if constexpr (NT > 0) {
-        for (int c = lane; c < span; c += 64) {
+    // this lane's face: face i of row r of the plane
+    const bool mine = wid < wpp && f < nfp;
+    const long long r = mine ? f / rowf : 0;
+    const int i = mine ? (int)(f - r * rowf) : 0;
+    const long long row = zb + r * g.sy + g.gx;             // interior cell 0 of the row
+    FaceBarLoad<NV> fl;
+    fl.load(rbar, C, row + i, row + i - 1, mine && i < g.nx, mine && i > 0);
+    for (int c = lane; c < span; c += 128) {
+        double a[NT], e[NT];
+        const bool two = c + 64 < span;
+        vjp_load<NV>(U, P, C, base0 + c, a);
+        if (two) vjp_load<NV>(U, P, C, base0 + c + 64, e);
 #pragma unroll
-            for (int q = 0; q < NV; ++q) tile[q * W + c] = U[q * C + base0 + c];
+        for (int q = 0; q < NT; ++q) tile[q * W + c] = R(a[q]);
+        if (two) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) tile[(NV + k) * W + c] = P[k * C + base0 + c];
+            for (int q = 0; q < NT; ++q) tile[q * W + c + 64] = R(e[q]);
+        }
+    }
+    const bool any = fl.keep(bars, lane, g.idx);
+    __syncthreads();
+    if (mine && any) {
+        const int off = (int)(row + i - 3 - base0);
+        const SinkLds<R> sk{(lds_double *)w, W, off, 1, NV * W};
+        if constexpr (vjp_from_memory<NS, R>()) {
+            const Stencil st{U, P, row + i - 3, 1, C};
+            vjp_face<NS, R, 0, CU6>(st, th, FaceBarMem{rbar, C, row + i, row + i - 1, i < g.nx, i > 0, g.idx}, sk, ds);
+        } else {
+            const StencilLds<NV, R> st{(const __attribute__((address_space(3))) R *)tile, off, 1, W};
+            const FaceBar<R> fb{(const __attribute__((address_space(3))) R *)bars + lane};
+            vjp_face<NS, R, 0, CU6>(st, th, fb, sk, ds);
         }
     }
     __syncthreads();
-    if (wid < wpp && f < nfp) {
-        const long long r = f / rowf;
-        const int i = (int)(f - r * rowf);
-        const long long row = zb + r * g.sy + g.gx;             // interior cell 0 of the row
-        const FaceBar fb{rbar, C, row + i, row + i - 1, i < g.nx, i > 0, g.idx};
-        bool any = false;
-#pragma unroll
-        for (int q = 0; q < NV; ++q) any = any || (fb(q) != 0.0);
-        if (any) {
-            const long long base = row + i - 3;
-            SinkLds sk{(volatile lds_double *)w, W, (int)(base - base0), 1, NV * W};
-            if constexpr (NT > 0) {
-                const StencilLds<NV> st{(const lds_double *)tile, (int)(base - base0), 1, W};
-                face_vjp<NS, R, 0, CU6>(st, th, fb, sk, ds);
-            } else {
-                const Stencil st{U, P, base, 1, C};
-                face_vjp<NS, R, 0, CU6>(st, th, fb, sk, ds);
-            }
-        }
+    for (int c = lane; c < span; c += 128) {
+        const bool two = c + 64 < span;
+        VjpMerge<NV> a, e;
+        a.load(Ubar, Pbar, C, base0 + c);
+        if (two) e.load(Ubar, Pbar, C, base0 + c + 64);
+        a.store(Ubar, Pbar, C, base0 + c, [&](int q) { return w[q * W + c]; });
+        if (two) e.store(Ubar, Pbar, C, base0 + c + 64, [&](int q) { return w[q * W + c + 64]; });
     }
-    __syncthreads();
-    for (int c = lane; c < span; c += 64) {
-#pragma unroll
-        for (int q = 0; q < NV; ++q) Ubar[q * C + base0 + c] += w[q * W + c];
-#pragma unroll
-        for (int k = 0; k < kSinkExtra; ++k) Pbar[k * C + base0 + c] += w[(NV + k) * W + c];
-    }
-}
-
-// LDS bytes per wave of k_face_vjp_x for a run of W cells.
-template <int NS, typename R>
-constexpr size_t vjp_x_lds_per_wave(int W) {
-    return (size_t)(NS + 4 + kSinkExtra + (vjp_staged<R>() ? NS + 8 : 0)) * W * sizeof(double);
 }
 
 // ---------------------------------------------------------------------------
@@ -735,8 +842,8 @@ constexpr size_t vjp_x_lds_per_wave(int W) {
 // windows that cover it in wave order to Ubar / Pbar (one coalesced
 // read-modify-write per cell and field).  Blocks b and b + 1 share five
 // rows, blocks b and b + 2 none: launch `phase` takes the blocks
-// b = phase mod 2.  Staged (FP64): the block first copies the U and
-// primitives of its (F + 5) x 16 cells into LDS.
+// b = phase mod 2.  The block first copies the U and primitives of its
+// (F + 5) x 16 cells and its face cotangents into LDS.
 // ---------------------------------------------------------------------------
 constexpr int kVjpTX = 16, kVjpWin = kVjpTX * 9;
 // Waves per y/z block (four faces each): two in FP64, so that two blocks of
@@ -747,7 +854,7 @@ constexpr int kVjpTX = 16, kVjpWin = kVjpTX * 9;
 // of at least five faces keep next-but-one neighbours disjoint (two launch
 // groups).
 template <typename R>
-constexpr int vjp_yz_waves() { return sizeof(R) == 8 ? 2 : 4; }
+constexpr int vjp_yz_waves() { return 2; }
 template <typename R>
 constexpr int vjp_yz_faces() { return 4 * vjp_yz_waves<R>(); }
 static_assert(vjp_yz_faces<double>() >= 5 && vjp_yz_faces<float>() >= 5, "windows of blocks b and b + 2 must not meet");
@@ -758,11 +865,12 @@ __global__ __launch_bounds__(64 * vjp_yz_waves<R>()) __attribute__((amdgpu_waves
     double *__restrict__ Ubar, double *__restrict__ Pbar, Geo g, ThermoK<R> th, int phase, Dissip ds) {
     constexpr int NV = NS + 4;
     constexpr int NW = NV + kSinkExtra;                    // window rows
-    constexpr int NT = vjp_staged<R>() ? NV + 4 : 0;       // staged rows
+    constexpr int NT = NV + 4;                             // staged rows
     constexpr int WY = vjp_yz_waves<R>(), kVjpFB = vjp_yz_faces<R>(), kVjpRows = kVjpFB + 5;
     constexpr int TS = kVjpRows * kVjpTX;                  // staged cells
     __shared__ double xf_wyz[WY][NW * kVjpWin];
-    __shared__ double xf_tile[NT > 0 ? NT * TS : 1];
+    __shared__ R xf_tile[NT * TS];
+    __shared__ R xf_bars[WY][NV * 64];
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int tx = lane & (kVjpTX - 1), ts = lane / kVjpTX;
     const int nsw = DIR == 1 ? g.ny : g.nz;
@@ -779,39 +887,50 @@ __global__ __launch_bounds__(64 * vjp_yz_waves<R>()) __attribute__((amdgpu_waves
     // padded index of the cell at x = x0 + tx, interior sweep index 0, in this plane
     const long long col0 = (long long)g.gx + (DIR == 1 ? (long long)(g.gz + tr) * g.sz : (long long)(g.gy + tr) * g.sy) +
                            (long long)gs * ss;
-    volatile double *w = xf_wyz[wv];
+    double *w = xf_wyz[wv];
     for (int i = lane; i < NW * kVjpWin; i += 64) w[i] = 0.0;
-    if constexpr (NT > 0) {
+    const bool mine = x < g.nx && j <= nsw;
+    const long long col = col0 + x;
+    FaceBarLoad<NV> fl;
+    fl.load(rbar, C, col + (long long)j * ss, col + (long long)(j - 1) * ss, mine && j < nsw, mine && j > 0);
+    {
         // tile row r = sweep row j0 - 3 + r; cells past the padded extent are never read
-        for (int e = threadIdx.x; e < TS; e += 64 * WY) {
+        static_assert(TS <= 2 * 64 * WY, "two cells a thread");
+        auto at = [&](int e, long long &cell) {
             const int r = e / kVjpTX, cx = xi * kVjpTX + (e % kVjpTX);
-            if (cx >= g.nx || j0 - 3 + r > nsw + 2) continue;
-            const long long cell = col0 + cx + (long long)(j0 - 3 + r) * ss;
+            cell = col0 + cx + (long long)(j0 - 3 + r) * ss;
+            return e < TS && cx < g.nx && j0 - 3 + r <= nsw + 2;
+        };
+        double a[NT], e[NT];
+        long long ca, ce;
+        const int ta = threadIdx.x, te = ta + 64 * WY;
+        const bool ha = at(ta, ca), he = at(te, ce);
+        if (ha) vjp_load<NV>(U, P, C, ca, a);
+        if (he) vjp_load<NV>(U, P, C, ce, e);
+        if (ha) {
 #pragma unroll
-            for (int q = 0; q < NV; ++q) xf_tile[q * TS + e] = U[q * C + cell];
+            for (int q = 0; q < NT; ++q) xf_tile[q * TS + ta] = R(a[q]);
+        }
+        if (he) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) xf_tile[(NV + k) * TS + e] = P[k * C + cell];
+            for (int q = 0; q < NT; ++q) xf_tile[q * TS + te] = R(e[q]);
         }
     }
+    const bool any = fl.keep(xf_bars[wv], lane, DIR == 1 ? g.idy : g.idz);
     __syncthreads();
-    if (x < g.nx && j <= nsw) {
-        const long long col = col0 + x;
-        const FaceBar fb{rbar, C, col + (long long)j * ss, col + (long long)(j - 1) * ss, j < nsw, j > 0,
-                         DIR == 1 ? g.idy : g.idz};
-        bool any = false;
-#pragma unroll
-        for (int q = 0; q < NV; ++q) any = any || (fb(q) != 0.0);
-        if (any) {
-            // window row r of wave w = sweep row j0 + 4w - 3 + r; stencil cell m is row ts + m
-            SinkLds sk{(volatile lds_double *)xf_wyz[wv], kVjpWin, ts * kVjpTX + tx, kVjpTX, NV * kVjpWin};
-            if constexpr (NT > 0) {
-                // stencil cell m of face j is tile row j - j0 + m
-                const StencilLds<NV> st{(const lds_double *)xf_tile, (4 * wv + ts) * kVjpTX + tx, kVjpTX, TS};
-                face_vjp<NS, R, DIR, CU6>(st, th, fb, sk, ds);
-            } else {
-                const Stencil st{U, P, col + (long long)(j - 3) * ss, ss, C};
-                face_vjp<NS, R, DIR, CU6>(st, th, fb, sk, ds);
-            }
+    if (mine && any) {
+        // window row r of wave w = sweep row j0 + 4w - 3 + r; stencil cell m is row ts + m
+        const SinkLds<R> sk{(lds_double *)xf_wyz[wv], kVjpWin, ts * kVjpTX + tx, kVjpTX, NV * kVjpWin};
+        if constexpr (vjp_from_memory<NS, R>()) {
+            const FaceBarMem fb{rbar, C, col + (long long)j * ss, col + (long long)(j - 1) * ss, j < nsw, j > 0,
+                                DIR == 1 ? g.idy : g.idz};
+            vjp_face<NS, R, DIR, CU6>(Stencil{U, P, col + (long long)(j - 3) * ss, ss, C}, th, fb, sk, ds);
+        } else {
+            // stencil cell m of face j is tile row j - j0 + m
+            const StencilLds<NV, R> st{(const __attribute__((address_space(3))) R *)xf_tile, (4 * wv + ts) * kVjpTX + tx,
+                                       kVjpTX, TS};
+            const FaceBar<R> fb{(const __attribute__((address_space(3))) R *)xf_bars[wv] + lane};
+            vjp_face<NS, R, DIR, CU6>(st, th, fb, sk, ds);
         }
     }
     __syncthreads();
@@ -822,15 +941,13 @@ __global__ __launch_bounds__(64 * vjp_yz_waves<R>()) __attribute__((amdgpu_waves
         if (cx >= g.nx || row > nsw + 2) continue;
         const int wlo = r >= 8 ? (r - 8 + 3) / 4 : 0, whi = min(WY - 1, r / 4);
         const long long cell = col0 + cx + (long long)row * ss;
-#pragma unroll
-        for (int q = 0; q < NW; ++q) {
+        VjpMerge<NV> m;
+        m.load(Ubar, Pbar, C, cell);
+        m.store(Ubar, Pbar, C, cell, [&](int q) {
             double v = 0.0;
             for (int ww = wlo; ww <= whi; ++ww) v += xf_wyz[ww][q * kVjpWin + (r - 4 * ww) * kVjpTX + (c % kVjpTX)];
-            if (q < NV)
-                Ubar[q * C + cell] += v;
-            else
-                Pbar[(q - NV) * C + cell] += v;
-        }
+            return v;
+        });
     }
 }
 
