@@ -243,17 +243,13 @@ int viscous_into(xf_ctx *c, const double *U, const Prim &pb, double *const out[3
     return XF_OK;
 }
 
-// GLF speeds of the active directions from the primitives just computed; a
-// no-op for the other artificial viscosities.
-hipError_t glf_speeds(xf_ctx *c, const double *U, const double *P, unsigned long long *mx, hipStream_t s) {
+// Where a primitive pass puts the GLF speeds (zeroed here), or null for the
+// other artificial viscosities.
+hipError_t glf_target(xf_ctx *c, unsigned long long *mx, unsigned long long **to, hipStream_t s) {
+    *to = nullptr;
     if (c->lc.visc != XF_VISC_GLF) return hipSuccess;
-    const int n[3] = {c->lc.g.nx, c->lc.g.ny, c->lc.g.nz};
-    return timed(c, XF_K_CFL, s, [&] {
-        hipError_t e = xf::launch_reset_u64(mx + 1, 9, s);
-        for (int d = 0; d < 3 && e == hipSuccess; ++d)
-            if (n[d] > 1) e = c->ops->glf(c->lc, d, U, P, mx + 1 + 3 * d, s);
-        return e;
-    });
+    *to = mx + 1;
+    return timed(c, XF_K_CFL, s, [&] { return xf::launch_reset_u64(mx + 1, 9, s); });
 }
 
 const double *glf_of(const xf_ctx *c, const unsigned long long *mx, int d) {
@@ -265,12 +261,13 @@ const double *glf_of(const xf_ctx *c, const unsigned long long *mx, int d) {
 // takes the CFL maximum into *cfl (zeroed beforehand)
 hipError_t prims(xf_ctx *c, const double *U, const Prim &pb, hipStream_t s, bool p64 = true, double *Ug = nullptr,
                  unsigned long long *cfl = nullptr) {
+    unsigned long long *glf;
+    const hipError_t e = glf_target(c, pb.mx, &glf, s);
+    if (e != hipSuccess) return e;
     // viscous contexts: every padded cell (the tangential derivatives read edge ghosts)
-    hipError_t e = timed(c, XF_K_PRIMS, s, [&] {
-        return c->ops->prims(c->lc, U, p64 ? pb.P : nullptr, pb.Uf, pb.Pf, c->viscous ? 1 : 0, Ug, cfl, s);
+    return timed(c, XF_K_PRIMS, s, [&] {
+        return c->ops->prims(c->lc, U, p64 ? pb.P : nullptr, pb.Uf, pb.Pf, c->viscous ? 1 : 0, Ug, cfl, glf, s);
     });
-    if (e == hipSuccess) e = glf_speeds(c, U, pb.P, pb.mx, s);
-    return e;
 }
 
 // The active sweeps into rhs, z, then y, then x.  FP64 contexts accumulate
@@ -371,8 +368,10 @@ int rhs_vjp_into(xf_ctx *c, const double *U, const double *rbar, double *Ubar, d
                  unsigned long long *mx, hipStream_t s) {
     const LaunchCtx &lc = c->lc;
     const int n[3] = {lc.g.nx, lc.g.ny, lc.g.nz};
-    XF_TRY(timed(c, XF_K_PRIMS, s, [&] { return c->ops->prims(lc, U, P, nullptr, nullptr, 0, nullptr, nullptr, s); }));
-    XF_TRY(glf_speeds(c, U, P, mx, s));
+    unsigned long long *glf;
+    XF_TRY(glf_target(c, mx, &glf, s));
+    XF_TRY(timed(c, XF_K_PRIMS, s,
+                 [&] { return c->ops->prims(lc, U, P, nullptr, nullptr, 0, nullptr, nullptr, glf, s); }));
     XF_TRY(timed(c, XF_K_ZERO, s, [&] { return xf::launch_zero(3 * lc.g.cells, Pbar, s); }));
     for (int d = 0; d < 3; ++d) {
         if (n[d] <= 1) continue;
@@ -663,7 +662,7 @@ int xf_rhs_alpha(xf_ctx *c, const double *U, const double *alpha_in, double *alp
 int xf_primitives(xf_ctx *c, const double *U, double *prim, void *stream) {
     if (!c || !U || !prim || !aligned8(U) || !aligned8(prim)) return XF_EINVAL;
     const hipStream_t s = (hipStream_t)stream;
-    XF_TRY(timed(c, XF_K_PRIMS, s, [&] { return c->ops->prims(c->lc, U, prim, nullptr, nullptr, 1, nullptr, nullptr, s); }));
+    XF_TRY(timed(c, XF_K_PRIMS, s, [&] { return c->ops->prims(c->lc, U, prim, nullptr, nullptr, 1, nullptr, nullptr, nullptr, s); }));
     return XF_OK;
 }
 
@@ -673,7 +672,7 @@ int xf_cfl_dt(xf_ctx *c, const double *U, double cfl, double *dt_dev, void *ws, 
     const hipStream_t s = (hipStream_t)stream;
     double *P = at<double>(ws, l.P);
     unsigned long long *mx = at<unsigned long long>(ws, l.mx);
-    XF_TRY(timed(c, XF_K_PRIMS, s, [&] { return c->ops->prims(c->lc, U, P, nullptr, nullptr, 0, nullptr, nullptr, s); }));
+    XF_TRY(timed(c, XF_K_PRIMS, s, [&] { return c->ops->prims(c->lc, U, P, nullptr, nullptr, 0, nullptr, nullptr, nullptr, s); }));
     XF_TRY(timed(c, XF_K_CFL, s, [&] {
         hipError_t e = xf::launch_cfl_reset(mx, s);
         if (e == hipSuccess) e = c->ops->cfl(c->lc, U, P, mx, s);
@@ -740,9 +739,9 @@ int flow_rk3_step(xf_ctx *c, double *U, double dt, const double *dt_in, double c
     double *out[3] = {S1, S2, U};
     const double a[3] = {0.0, 0.75, 1.0 / 3.0};
     const double b[3] = {1.0, 0.25, 2.0 / 3.0};
-    // a mixed step without viscous terms or GLF needs only the FP32 copies
-    // (the CFL maximum comes from the primitive pass itself)
-    const bool p64 = !mixed || c->viscous || lc.visc == XF_VISC_GLF;
+    // a mixed step without viscous terms needs only the FP32 copies (the CFL
+    // maximum and the GLF speeds come from the primitive pass itself)
+    const bool p64 = !mixed || c->viscous;
     // the primitive pass fills the ghosts of the stage input itself: the
     // face ghosts, and with viscous terms (whose tangential derivatives read
     // them) the edge and corner ghosts too; the state's ghosts are filled in
@@ -953,15 +952,14 @@ int xf_rk3_step_vjp(xf_ctx *c, const double *Un, double dt, double *Ubar, void *
     double *P = pb.P, *Pbar = at<double>(ws, l.Pbar), *L = mixed ? nullptr : at<double>(ws, l.L);
     double *V0 = at<double>(ws, l.V0), *V1 = at<double>(ws, l.V1), *V2 = at<double>(ws, l.V2);
     double *lam0 = at<double>(ws, l.lam0), *mu = at<double>(ws, l.mu);
-    const bool p64 = !mixed || lc.visc == XF_VISC_GLF;
     int r;
     // forward stage states V0 = G(U_n), V1 = G(V0 + dt L(V0)), V2 = G(3/4 V0 + 1/4 (V1 + dt L(V1)))
     XF_TRY(timed(c, XF_K_STAGE, s, [&] { return xf::launch_copy(n, Un, V0, s); }));
     XF_TRY(fill(c, V0, s));
-    XF_TRY(prims(c, V0, pb, s, p64));
+    XF_TRY(prims(c, V0, pb, s, !mixed));
     if ((r = stage_into(c, V0, V1, V0, 0.0, 1.0, dt, nullptr, pb, L, nullptr, s)) != XF_OK) return r;
     XF_TRY(fill(c, V1, s));
-    XF_TRY(prims(c, V1, pb, s, p64));
+    XF_TRY(prims(c, V1, pb, s, !mixed));
     if ((r = stage_into(c, V1, V2, V0, 0.75, 0.25, dt, nullptr, pb, L, nullptr, s)) != XF_OK) return r;
     XF_TRY(fill(c, V2, s));
     // reverse sweep through the stages

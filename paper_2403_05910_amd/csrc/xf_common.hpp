@@ -38,6 +38,14 @@ __device__ __forceinline__ int ghost_src(int bc, int sd, int l, int n, int ng) {
     return bc == XF_BC_PERIODIC ? ng + l : ng + n - 1;
 }
 
+// Padded index along one axis of the cell that padded index c holds: itself
+// in the interior, its source in the ghost layers (ng = 0: no ghosts).
+__device__ __forceinline__ int ghost_map(int c, int n, int ng, int lo, int hi) {
+    if (c < ng) return ghost_src(lo, 0, c, n, ng);
+    if (c >= ng + n) return ghost_src(hi, 1, c - ng - n, n, ng);
+    return c;
+}
+
 // Species thermo in the form the kernels evaluate (Horner in T):
 //   cv_s(T) = sum_k cv[s][k] T^k  (k = 0..4),  C_v,s = C_p,s - R_s
 //   e_s(T)  = sum_k e[s][k] T^k   (k = 0..5),  e_s = h_s - R_s T
@@ -140,8 +148,11 @@ struct NsOps {
     // corner ghosts lie outside every stencil and are left)
     // With cfl, the pass also folds the CFL rate of its interior cells
     // (Eq. 17, as the cfl entry) into *cfl, which the caller has zeroed.
+    // With glf, the GLF speeds of the active directions, the largest |u_d - c|,
+    // |u_d|, |u_d + c| over every cell direction d's stencils read, into
+    // glf[3 d .. 3 d + 2] (uint64 bits of positive doubles; zeroed beforehand).
     hipError_t (*prims)(const LaunchCtx &, const double *U, double *P, float *Uf, float *Pf, int all_cells,
-                        double *Ug, unsigned long long *cfl, hipStream_t);
+                        double *Ug, unsigned long long *cfl, unsigned long long *glf, hipStream_t);
     // one direction of the convective flux difference.  FP64 sweeps read U,
     // P and write rhs (accumulate: rhs +=, else rhs =); mixed-precision
     // sweeps read Uf, Pf and write the FP32 differences to rhs32 (no
@@ -164,10 +175,6 @@ struct NsOps {
     // direction, FP64, into alpha [3][astride] (glf: the direction's GLF speeds)
     hipError_t (*face_speeds)(const LaunchCtx &, int dir, const double *U, const double *P, const double *glf,
                               double *alpha, long long astride, hipStream_t);
-    // GLF speeds of one direction: atomicMax of |u_d - c|, |u_d|, |u_d + c|
-    // (uint64 bits of positive doubles) into mx[0..2], which must start at 0
-    hipError_t (*glf)(const LaunchCtx &, int dir, const double *U, const double *P, unsigned long long *mx,
-                      hipStream_t);
     // VJP of the primitive map: Ubar += (d(p, T, rho)/dU)^T Pbar
     hipError_t (*prims_vjp)(const LaunchCtx &, const double *U, const double *P,
                             const double *Pbar, double *Ubar, hipStream_t);

@@ -17,10 +17,10 @@ constexpr int NS = XF_NS;
 unsigned blocks_for(long long n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 
 hipError_t prims(const LaunchCtx &c, const double *U, double *P, float *Uf, float *Pf, int all_cells, double *Ug,
-                 unsigned long long *cfl, hipStream_t s) {
+                 unsigned long long *cfl, unsigned long long *glf, hipStream_t s) {
     if (Ug && Ug != U) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_prims<NS>, dim3(blocks_for(c.g.cells, 256)), dim3(256), 0, s, U, P, c.g, c.th64,
-                       c.status, Uf, Pf, all_cells, Ug, cfl);
+                       c.status, Uf, Pf, all_cells, Ug, cfl, glf);
     return hipGetLastError();
 }
 
@@ -257,16 +257,6 @@ hipError_t sweep_vjp(const LaunchCtx &c, int dir, const double *U, const double 
     return sweep_vjp_t<double>(c, c.th64, dir, U, P, rbar, Ubar, Pbar, ds, s);
 }
 
-hipError_t glf(const LaunchCtx &c, int dir, const double *U, const double *P, unsigned long long *mx,
-               hipStream_t s) {
-    const Geo &g = c.g;
-    const long long n = (long long)(dir == 0 ? g.px : g.nx) * (dir == 1 ? g.py : g.ny) * (dir == 2 ? g.pz : g.nz);
-    long long nb = blocks_for(n, 256);
-    if (nb > 2048) nb = 2048;   // grid-stride: three atomics per block
-    hipLaunchKernelGGL(k_glf<NS>, dim3((unsigned)nb), dim3(256), 0, s, U, P, g, dir, mx);
-    return hipGetLastError();
-}
-
 hipError_t prims_vjp(const LaunchCtx &c, const double *U, const double *P, const double *Pbar, double *Ubar,
                      hipStream_t s) {
     hipLaunchKernelGGL(k_prims_vjp<NS>, dim3(blocks_for(c.g.cells, 256)), dim3(256), 0, s, U, P, Pbar, Ubar, c.g,
@@ -308,7 +298,7 @@ hipError_t viscous(const LaunchCtx &c, int dir, const double *U, const double *P
     return hipGetLastError();
 }
 
-const NsOps kOps = {prims, sweep, sweep_vjp, sweep_frozen, face_speeds, glf, prims_vjp, cfl, transport, viscous, react_launch<NS>,
+const NsOps kOps = {prims, sweep, sweep_vjp, sweep_frozen, face_speeds, prims_vjp, cfl, transport, viscous, react_launch<NS>,
                     few32<NS, float>() ? few32_stage : nullptr};
 
 }  // namespace
