@@ -494,6 +494,13 @@ int xf_create_ghosts(const xf_grid *grid, const xf_thermo *thermo, int precision
     g.idy = g.ny > 1 ? 1.0 / grid->dy : 0.0;
     g.idz = g.nz > 1 ? 1.0 / grid->dz : 0.0;
     for (int k = 0; k < 6; ++k) g.bc[k] = grid->bc[k];
+    g.small = g.cells < (1ll << 31);
+    g.dnx.set(g.nx);
+    g.dny.set(g.ny);
+    g.dpx.set(g.px);
+    g.dpy.set(g.py);
+    g.dnf.set(g.nx + 1);
+    g.dvf.set(g.nx + 3);
     fill_thermo(c->lc.th64, thermo);
     fill_thermo(c->lc.th32, thermo);
     c->lc.precision = precision;

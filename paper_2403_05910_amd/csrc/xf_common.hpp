@@ -17,6 +17,24 @@ constexpr int kMaxNs = XF_MAX_SPECIES;
 constexpr double kNewtonTol = 1e-11;
 constexpr int kNewtonMaxIt = 50;
 
+// Division by a number fixed on the host: quotients of n < 2^31 by one
+// multiplication (on uniform n by the scalar unit, which has no division; in
+// vector registers an integer division takes about 25 instructions, a 64-bit
+// one about 100).  With l = ceil(log2 d) and m = ceil(2^(31+l) / d), e = m d -
+// 2^(31+l) < d <= 2^l, so n e < 2^(31+l) and floor(n m / 2^(31+l)) is exact.
+struct FastDiv {
+    unsigned m, s;   // m = 0: d = 1
+    void set(long long d) {
+        m = s = 0;
+        if (d <= 1) return;
+        int l = 1;
+        while ((1ll << l) < d) ++l;
+        m = (unsigned)((((unsigned long long)1 << (31 + l)) + d - 1) / d);
+        s = l - 1;
+    }
+    __device__ __forceinline__ unsigned of(unsigned n) const { return m ? __umulhi(n, m) >> s : n; }
+};
+
 // Geometry of one padded SoA field: x fastest, 3 or 4 ghost layers per active axis.
 struct Geo {
     int nx, ny, nz;      // interior cells
@@ -27,7 +45,28 @@ struct Geo {
     double dx, dy, dz;
     double idx, idy, idz;
     int bc[6];
+    // cells < 2^31: linear indices decode by the quotients below (interior
+    // extents, padded extents, x faces and viscous x faces of a row)
+    int small;
+    FastDiv dnx, dny, dpx, dpy, dnf, dvf;
 };
+
+// (x, y, z) of linear index q over extents (a, b, ...), da and db their
+// quotients.
+__device__ __forceinline__ void split3(const Geo &g, long long q, int a, int b, const FastDiv &da, const FastDiv &db, int &x,
+                                       int &y, int &z) {
+    if (g.small) {
+        const unsigned r = da.of((unsigned)q), k = db.of(r);
+        x = (int)((unsigned)q - r * a);
+        y = (int)(r - k * b);
+        z = (int)k;
+    } else {
+        const long long r = q / a;
+        x = (int)(q - r * a);
+        z = (int)(r / b);
+        y = (int)(r - (long long)z * b);
+    }
+}
 
 // Padded source index (along the ghost's axis) of ghost layer l on side sd
 // (0 low, 1 high), n interior cells, ng ghost layers per side: periodic wraps,

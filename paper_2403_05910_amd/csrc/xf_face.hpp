@@ -231,17 +231,27 @@ XF_HD float weno7(float a, float b, float c, float d, float e, float f, float g)
 // logical blocks (blocks that share stencil rows then share one L2).
 constexpr int kNumXcd = 8;
 
+// dispatch order b of n blocks goes to XCD b % 8; gives consecutive logical
+// ids to the blocks one XCD receives (only when the count divides evenly)
+__device__ __forceinline__ unsigned xcd_linear(unsigned b, unsigned n) {
+    return n % kNumXcd == 0 ? (b % kNumXcd) * (n / kNumXcd) + b / kNumXcd : b;
+}
 __device__ __forceinline__ void xcd_block(unsigned &bx, unsigned &by, unsigned &bz) {
     const unsigned gx = gridDim.x, gy = gridDim.y, gz = gridDim.z;
-    const unsigned n = gx * gy * gz;
-    const unsigned b = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
-    // dispatch order b goes to XCD b % 8; give consecutive logical ids to the
-    // blocks one XCD receives (only when the count divides evenly)
-    unsigned l = b;
-    if (n % kNumXcd == 0) l = (b % kNumXcd) * (n / kNumXcd) + b / kNumXcd;
+    const unsigned l = xcd_linear(blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z), gx * gy * gz);
     bx = l % gx;
     by = (l / gx) % gy;
     bz = l / (gx * gy);
+}
+// The same with the quotients of gridDim.x and gridDim.y given (grids of fewer
+// than 2^31 blocks).
+__device__ __forceinline__ void xcd_block(const FastDiv &dgx, const FastDiv &dgy, unsigned &bx, unsigned &by, unsigned &bz) {
+    const unsigned gx = gridDim.x, gy = gridDim.y, gz = gridDim.z;
+    const unsigned l = xcd_linear(blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z), gx * gy * gz);
+    const unsigned r = dgx.of(l);
+    bx = l - r * gx;
+    bz = dgy.of(r);
+    by = r - bz * gy;
 }
 
 // Read-only view of the stencil of one face along one axis (2 RAD cells:

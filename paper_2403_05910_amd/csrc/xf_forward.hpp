@@ -143,10 +143,8 @@ __global__ __launch_bounds__(256) void k_prims(const double *U, double *__restri
     double gv[9] = {};
     double sv = 0.0;   // with cfl: the cell's rate sum_d (|u_d| + c) / dx_d of Eq. 17 (interior cells)
     if (idx < g.cells) {
-        const int x = (int)(idx % g.px);
-        const long long r = idx / g.px;
-        const int y = (int)(r % g.py);
-        const int z = (int)(r / g.py);
+        int x, y, z;
+        split3(g, idx, g.px, g.py, g.dpx, g.dpy, x, y, z);
         const int ng = (x < g.gx || x >= g.gx + g.nx) + (y < g.gy || y >= g.gy + g.ny) +
                        (z < g.gz || z >= g.gz + g.nz);
         // edge and corner ghosts lie outside every stencil
@@ -518,7 +516,7 @@ __device__ __forceinline__ void stage_cells(const S *__restrict__ U, const S *__
 template <int NS, typename R, typename S, bool PP, int SPD, int REC, int MODE>
 __global__ __launch_bounds__(kXBlock) __attribute__((amdgpu_waves_per_eu(sweep_waves<R, REC, true, PP>()))) void k_sweep_x(
     const S *__restrict__ U, const S *__restrict__ P, R *__restrict__ rhs, Geo g, ThermoK<R> th, int accumulate,
-    StageArgs sa, unsigned *status, Dissip ds, int fpb) {
+    StageArgs sa, unsigned *status, Dissip ds, int fpb, FastDiv dw) {
     constexpr int NV = NS + 4;
     constexpr int RAD = stencil_radius(REC);
     constexpr int GAP = 2 * RAD - 1;
@@ -528,8 +526,7 @@ __global__ __launch_bounds__(kXBlock) __attribute__((amdgpu_waves_per_eu(sweep_w
     __shared__ R sF[EXCH ? 1 : NV][EXCH ? 1 : kXBlock];
     __shared__ R sEdge[2][EXCH ? NW : 1][EXCH ? NV : 1];
     __shared__ S xf_xstage[(NV + 4) * XC];
-    unsigned lb, u1, u2;
-    xcd_block(lb, u1, u2);
+    const unsigned lb = xcd_linear(blockIdx.x, gridDim.x);
     const int t = threadIdx.x;
     const long long nfx = (long long)g.nx + 1;
     const long long nfaces = nfx * g.ny * g.nz;
@@ -539,17 +536,15 @@ __global__ __launch_bounds__(kXBlock) __attribute__((amdgpu_waves_per_eu(sweep_w
     // the block's first face: face i0 of row row0 = (j0, k0); its faces lie
     // in rows row0 .. row0 + nseg - 1 (segment sg = row row0 + sg), so the
     // per-cell and per-face indexing below needs 32-bit divisions only
-    const long long row0 = f0 / nfx;
-    const int i0 = (int)(f0 - row0 * nfx);
-    const int j0 = (int)(row0 % g.ny);
-    const long long k0 = row0 / g.ny;
+    int i0, j0, k0;
+    split3(g, f0, g.nx + 1, g.ny, g.dnf, g.dny, i0, j0, k0);
     const int nfx32 = g.nx + 1;
     auto row_base = [&](int sg) {
-        int j = j0 + sg;
-        long long k = k0;
-        if (j >= g.ny) {
-            k += j / g.ny;
-            j %= g.ny;
+        int j = j0 + sg, k = k0;
+        if (j >= g.ny) {   // (j < ny + 257)
+            const int n = (int)g.dny.of((unsigned)j);
+            k += n;
+            j -= n * g.ny;
         }
         return (g.gz + k) * g.sz + (long long)(g.gy + j) * g.sy + g.gx;
     };
@@ -557,11 +552,11 @@ __global__ __launch_bounds__(kXBlock) __attribute__((amdgpu_waves_per_eu(sweep_w
         // staged cell e: segment sg = (e + i0) / W, W = nfx + GAP, x index
         // e + i0 - sg W - RAD of that row (segment 0 starts at face i0, the
         // others at face 0)
-        const int nseg = (int)(flast / nfx - row0) + 1;
+        const int nseg = (int)g.dnf.of((unsigned)(flast - f0) + i0) + 1;
         const int ncell = (int)(flast - f0 + 1) + nseg * GAP;
         const int W = nfx32 + GAP;
         auto at = [&](int e, long long &cell) {
-            const int sg = (e + i0) / W;
+            const int sg = (int)dw.of((unsigned)(e + i0));
             cell = row_base(sg) + (e + i0 - sg * W - RAD);
             return e < ncell;
         };
@@ -579,7 +574,7 @@ __global__ __launch_bounds__(kXBlock) __attribute__((amdgpu_waves_per_eu(sweep_w
     long long cell = 0;       // the cell below the face
     bool inner = false;       // and whether it is an interior one
     if (valid) {
-        const int sg = (t + i0) / nfx32, i = t + i0 - sg * nfx32;
+        const int sg = (int)g.dnf.of((unsigned)(t + i0)), i = t + i0 - sg * nfx32;
         cell = row_base(sg) + i - 1;
         inner = i > 0;
         // stencil cell m of face i (cell i - RAD + m of its row) is staged at
@@ -661,7 +656,7 @@ struct TileShape {
 template <int NS, typename R, int DIR, typename S, bool PP, int SPD, int REC, int MODE>
 __global__ __launch_bounds__((TileShape<R, REC, PP>::x * TileShape<R, REC, PP>::s)) __attribute__((amdgpu_waves_per_eu(sweep_waves<R, REC, false, PP>()))) void
 k_sweep_tile(const S *__restrict__ U, const S *__restrict__ P, R *__restrict__ rhs, Geo g, ThermoK<R> th,
-             int accumulate, StageArgs sa, unsigned *status, Dissip ds) {
+             int accumulate, StageArgs sa, unsigned *status, Dissip ds, FastDiv dgx, FastDiv dgy) {
     constexpr int NV = NS + 4;
     using Shape = TileShape<R, REC, PP>;
     constexpr int kTileX = Shape::x, kTileS = Shape::s;
@@ -681,7 +676,7 @@ k_sweep_tile(const S *__restrict__ U, const S *__restrict__ P, R *__restrict__ r
     __shared__ R sEdge[2][EXCH ? NWV : 1][EXCH ? NV : 1][EXCH ? kTileX : 1];
     __shared__ S xf_ftile[(NV + 4) * TSZ];
     unsigned bx, by, bz;
-    xcd_block(bx, by, bz);
+    xcd_block(dgx, dgy, bx, by, bz);
     const int tx = threadIdx.x, ts = threadIdx.y;
     const int x = bx * kTileX + tx;
     const int j0 = by * (kTileS - 1);                 // the tile's first face
@@ -765,9 +760,8 @@ __global__ __launch_bounds__(256) void k_cfl(const double *__restrict__ U, const
     double s = 0.0;
     for (long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x; q < n;
          q += (long long)gridDim.x * blockDim.x) {
-        const int i = (int)(q % g.nx);
-        const long long r = q / g.nx;
-        const int j = (int)(r % g.ny), k = (int)(r / g.ny);
+        int i, j, k;
+        split3(g, q, g.nx, g.ny, g.dnx, g.dny, i, j, k);
         const long long idx = (long long)(g.gz + k) * g.sz + (long long)(g.gy + j) * g.sy + (g.gx + i);
         const double rinv = P[3 * g.cells + idx], c = P[2 * g.cells + idx];
         double v = 0.0;

@@ -190,9 +190,8 @@ __global__ __launch_bounds__(256) void k_sum_dirs(double *rhs, const float *Lx, 
     const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= nint * nv) return;
     const long long f = q / nint, r = q - f * nint;
-    const int i = (int)(r % g.nx);
-    const long long r2 = r / g.nx;
-    const int j = (int)(r2 % g.ny), k = (int)(r2 / g.ny);
+    int i, j, k;
+    split3(g, r, g.nx, g.ny, g.dnx, g.dny, i, j, k);
     const long long o = f * g.cells + (long long)(g.gz + k) * g.sz + (long long)(g.gy + j) * g.sy + (g.gx + i);
     double L = 0.0;
     bool first = true;
@@ -254,9 +253,8 @@ __global__ __launch_bounds__(256) void k_vel_grad(const double *__restrict__ Q, 
     const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= g.cells) return;
     const long long C = g.cells;
-    const int x = (int)(idx % g.px);
-    const long long r = idx / g.px;
-    const int co[3] = {x, (int)(r % g.py), (int)(r / g.py)};
+    int co[3];
+    split3(g, idx, g.px, g.py, g.dpx, g.dpy, co[0], co[1], co[2]);
     const int n[3] = {g.nx, g.ny, g.nz}, p[3] = {g.px, g.py, g.pz};
     const long long st[3] = {1, g.sy, g.sz};
     const double ih[3] = {g.idx, g.idy, g.idz};

@@ -40,9 +40,12 @@ hipError_t launch_face_sweep(const LaunchCtx &c, const ThermoK<R> &th, int dir, 
         if constexpr (few32<NS, R>())
             hipLaunchKernelGGL((k_few32_x<NS, PP, SPD, REC>), dim3(nb), dim3(kXBlock), 0, s, U, P, rhs, g, th, accumulate,
                                sa, c.status, ds, fpb);
-        else
+        else {
+            FastDiv dw;
+            dw.set(nfx + 2 * stencil_radius(REC) - 1);
             hipLaunchKernelGGL((k_sweep_x<NS, R, S, PP, SPD, REC, XM>), dim3(nb), dim3(kXBlock), 0, s, U, P, rhs, g, th,
-                               accumulate, sa, c.status, ds, fpb);
+                               accumulate, sa, c.status, ds, fpb, dw);
+        }
         return hipGetLastError();
     }
     const int ntr = dir == 1 ? g.nz : g.ny;
@@ -50,6 +53,9 @@ hipError_t launch_face_sweep(const LaunchCtx &c, const ThermoK<R> &th, int dir, 
     constexpr int TX = TileShape<R, REC, PP>::x, TS = TileShape<R, REC, PP>::s;
     const unsigned tiles = (unsigned)((nsw + TS - 2) / (TS - 1));
     dim3 grid((g.nx + TX - 1) / TX, tiles, ntr), block(TX, TS);
+    FastDiv dgx, dgy;
+    dgx.set(grid.x);
+    dgy.set(grid.y);
     auto tile = [&](auto d) {
         constexpr int DIR = decltype(d)::value;
         if constexpr (few32<NS, R>())
@@ -57,7 +63,7 @@ hipError_t launch_face_sweep(const LaunchCtx &c, const ThermoK<R> &th, int dir, 
                                c.status, ds);
         else
             hipLaunchKernelGGL((k_sweep_tile<NS, R, DIR, S, PP, SPD, REC, MODE>), grid, block, 0, s, U, P, rhs, g, th,
-                               accumulate, sa, c.status, ds);
+                               accumulate, sa, c.status, ds, dgx, dgy);
     };
     if (dir == 1)
         tile(std::integral_constant<int, 1>{});

@@ -203,9 +203,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     const long long q = (long long)blockIdx.x * blockDim.x + t;
     const long long nint = (long long)g.nx * g.ny * g.nz;
     if (q >= nint) return;
-    const int i = (int)(q % g.nx);
-    const long long r2 = q / g.nx;
-    const int j = (int)(r2 % g.ny), k = (int)(r2 / g.ny);
+    int i, j, k;
+    split3(g, q, g.nx, g.ny, g.dnx, g.dny, i, j, k);
     const long long idx = (long long)(g.gz + k) * g.sz + (long long)(g.gy + j) * g.sy + (g.gx + i);
     const long long C = g.cells;
     double Y[NS];

@@ -229,12 +229,11 @@ __global__ __launch_bounds__(kViscXBlock) __attribute__((amdgpu_waves_per_eu(5))
     if (f0 >= nfaces) return;   // blocks that round the grid up to a multiple of 8
     const long long f = f0 + t;
     const bool valid = f < nfaces;
-    long long row = 0, rowbase = 0;
+    long long rowbase = 0;
     int kk = 0;
     if (valid) {
-        row = f / per_row;
-        kk = (int)(f - row * per_row);           // point face k = kk - 1, between cells kk - 2 and kk - 1
-        const int j = (int)(row % g.ny), k = (int)(row / g.ny);
+        int j, k;                                // point face k = kk - 1, between cells kk - 2 and kk - 1
+        split3(g, f, g.nx + 3, g.ny, g.dvf, g.dny, kk, j, k);
         rowbase = (long long)(g.gz + k) * g.sz + (long long)(g.gy + j) * g.sy + g.gx;
         double F[NV];
         visc_point_flux<NS, 0>(U, P, Q, G, rowbase + kk - 3, 1, g, th, g.idx / 24.0, terms, F);
