@@ -500,7 +500,7 @@ int xf_create_ghosts(const xf_grid *grid, const xf_thermo *thermo, int precision
     g.dpx.set(g.px);
     g.dpy.set(g.py);
     g.dnf.set(g.nx + 1);
-    g.dvf.set(g.nx + 3);
+    g.dvf.set(g.nx + 6);
     fill_thermo(c->lc.th64, thermo);
     fill_thermo(c->lc.th32, thermo);
     c->lc.precision = precision;

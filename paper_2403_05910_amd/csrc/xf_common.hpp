@@ -46,7 +46,7 @@ struct Geo {
     double idx, idy, idz;
     int bc[6];
     // cells < 2^31: linear indices decode by the quotients below (interior
-    // extents, padded extents, x faces and viscous x faces of a row)
+    // extents, padded extents, x faces of a row, and its cells with three ghosts a side)
     int small;
     FastDiv dnx, dny, dpx, dpy, dnf, dvf;
 };

@@ -288,15 +288,15 @@ hipError_t viscous(const LaunchCtx &c, int dir, const double *U, const double *P
                    double *rhs, int terms, hipStream_t s) {
     const Geo &g = c.g;
     if (dir == 0) {
-        const long long nf = ((long long)g.nx + 3) * g.ny * g.nz;
-        unsigned nb = (unsigned)((nf - 3 + (kViscXBlock - 4)) / (kViscXBlock - 3));   // blocks overlap by three
+        const long long n = ((long long)g.nx + 6) * g.ny * g.nz;
+        unsigned nb = (unsigned)((n - 6 + (kViscXBlock - 7)) / (kViscXBlock - 6));   // blocks overlap by six
         nb = (nb + kNumXcd - 1) / kNumXcd * kNumXcd;
         hipLaunchKernelGGL(k_visc_x<NS>, dim3(nb), dim3(kViscXBlock), 0, s, U, P, Q, G, rhs, g, c.th64, terms);
         return hipGetLastError();
     }
     const int nsw = dir == 1 ? g.ny : g.nz;
     const int ntr = dir == 1 ? g.nz : g.ny;
-    dim3 grid((g.nx + kViscTX - 1) / kViscTX, (nsw + kViscTS - 4) / (kViscTS - 3), ntr), block(kViscTX, kViscTS);
+    dim3 grid((g.nx + kViscTX - 1) / kViscTX, (nsw + kViscTS - 7) / (kViscTS - 6), ntr), block(kViscTX, kViscTS);
     if (dir == 1)
         hipLaunchKernelGGL((k_visc_tile<NS, 1>), grid, block, 0, s, U, P, Q, G, rhs, g, c.th64, terms);
     else

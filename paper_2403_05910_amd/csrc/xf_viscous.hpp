@@ -121,43 +121,90 @@ XF_HD double fv_normal(double a0, double a1, double a2, double a3, double i24h) 
     return (a0 - 27.0 * a1 + 27.0 * a2 - a3) * i24h;
 }
 
-// cells m = 0..3 at c0 + m step (cells i-1..i+2 of the face between i and
-// i+1); F[0..NS+3] receives the point flux in conservative field order
-template <int NS, int DIR>
-__device__ __forceinline__ void visc_point_flux(const double *__restrict__ U, const double *__restrict__ P,
-                                                const double *__restrict__ Q, const double *__restrict__ G,
-                                                long long c0, long long step, const Geo &g,
-                                                const ThermoK<double> &th, double i24h, int terms, double *F) {
+// One block's cells along the sweep axis, thread t one cell, neighbours along
+// the axis W threads apart: the cells' fields go to LDS, threads with a face
+// (between the cells at t + W and t + 2 W) form its point flux from the four
+// cells t..t + 3 W, and threads with fin add their own cell's residual from
+// the point fluxes of t - 3 W..t.  cell: the thread's cell (in the padded
+// grid also where it neither owns a face nor finishes).
+//
+// What bounds it: memory.  A face needs 4 (2 NS + 11) values; read from global
+// memory face by face, those loads went out in groups as registers allowed and
+// the kernels waited on them (x 384, y 509, z 522 us a pass at nine species and
+// 2.9 M cells, against 295 us for the bytes).  Staged, each cell's fields are
+// loaded once by its own thread, most of them before the first wait, and the species'
+// enthalpies and mass fractions are formed once a cell instead of four times:
+// x 295, y 320, z 310 us.  The diffusion coefficients, needed last, are asked for
+// after the first fields have gone to LDS: all at once spill (y 366 us).
+template <int NS>
+struct ViscStage {
+    static constexpr int kFields = NS + 10 > 2 * NS + 1 ? NS + 10 : 2 * NS + 1;   // and >= NS + 4 fluxes
+};
+
+template <int NS, int DIR, int NT, int W>
+__device__ __forceinline__ void visc_block(const double *__restrict__ U, const double *__restrict__ P,
+                                           const double *__restrict__ Q, const double *__restrict__ G,
+                                           double *__restrict__ rhs, const Geo &g, const ThermoK<double> &th,
+                                           int terms, double id, double (*S)[NT], int t, long long cell, bool face,
+                                           bool fin) {
+    constexpr int NV = NS + 4;
     const long long C = g.cells;
     constexpr int T1 = Axes<DIR>::t1, T2 = Axes<DIR>::t2;
     const bool a1 = (T1 == 0 ? g.nx : T1 == 1 ? g.ny : g.nz) > 1;
     const bool a2 = (T2 == 0 ? g.nx : T2 == 1 ? g.ny : g.nz) > 1;
-    long long c[4];
+    const bool stress = terms & kViscousStress, heat = terms & kViscousHeat, diff = terms & kViscousDiffusion;
+    const double i24h = id / 24.0;
+    auto fc = [&](int f) { return fv_face(S[f][t], S[f][t + W], S[f][t + 2 * W], S[f][t + 3 * W]); };
+    auto nd = [&](int f) { return fv_normal(S[f][t], S[f][t + W], S[f][t + 2 * W], S[f][t + 3 * W], i24h); };
+    const double T = P[cell];
+    double A[9] = {}, y[NS], D[NS], rho = 0.0;
+    if (stress) {
+        A[0] = Q[cell];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) c[m] = c0 + m * step;
-    auto fc = [&](const double *A) { return fv_face(A[c[0]], A[c[1]], A[c[2]], A[c[3]]); };
-    auto nd = [&](const double *A) { return fv_normal(A[c[0]], A[c[1]], A[c[2]], A[c[3]], i24h); };
+        for (int k = 0; k < 3; ++k) A[1 + k] = Q[(2 + k) * C + cell];
+        // tangential derivatives: d u_DIR / d x_t and d u_t / d x_t
+        if (a1) A[4] = G[(3 * T1 + DIR) * C + cell], A[5] = G[(3 * T1 + T1) * C + cell];
+        if (a2) A[6] = G[(3 * T2 + DIR) * C + cell], A[7] = G[(3 * T2 + T2) * C + cell];
+    }
+    if (heat) A[8] = Q[C + cell];
+    if (diff) {
+        const double rinv = P[3 * C + cell];
 #pragma unroll
-    for (int q = 0; q < NS + 4; ++q) F[q] = 0.0;
-    if (terms & kViscousStress) {
-        const double mu = fc(Q);
-        double uf[3], dn[3];
+        for (int s = 0; s < NS; ++s) {
+            y[s] = U[s * C + cell];
+        }
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            rho += y[s];
+            y[s] *= rinv;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 9; ++q) S[q][t] = A[q];
+    S[9][t] = T;
+    if (diff) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) S[10 + s][t] = e_species(th, s, T) + th.Rs[s] * T;
+        XF_FENCE();
+#pragma unroll
+        for (int s = 0; s < NS; ++s) D[s] = Q[(5 + s) * C + cell];
+    }
+    __syncthreads();
+    double F[NV], hf[NS];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) F[q] = 0.0;
+    if (face && stress) {
+        const double mu = fc(0);
+        double uf[3], Gf[3][3] = {};            // Gf[a][b] = d u_b / d x_a, the entries used
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            uf[k] = fc(Q + (2 + k) * C);
-            dn[k] = nd(Q + (2 + k) * C);      // d u_k / d x_DIR
+            uf[k] = fc(1 + k);
+            Gf[DIR][k] = nd(1 + k);
         }
-        // tangential derivatives at the face: d u_DIR / d x_t and d u_t / d x_t
-        const double t1n = a1 ? fc(G + (3 * T1 + DIR) * C) : 0.0, t1t = a1 ? fc(G + (3 * T1 + T1) * C) : 0.0;
-        const double t2n = a2 ? fc(G + (3 * T2 + DIR) * C) : 0.0, t2t = a2 ? fc(G + (3 * T2 + T2) * C) : 0.0;
-        double Gf[3][3] = {};                   // Gf[a][b] = d u_b / d x_a, the entries used
-        Gf[DIR][0] = dn[0];
-        Gf[DIR][1] = dn[1];
-        Gf[DIR][2] = dn[2];
-        Gf[T1][DIR] = t1n;
-        Gf[T1][T1] = t1t;
-        Gf[T2][DIR] = t2n;
-        Gf[T2][T2] = t2t;
+        Gf[T1][DIR] = a1 ? fc(4) : 0.0;
+        Gf[T1][T1] = a1 ? fc(5) : 0.0;
+        Gf[T2][DIR] = a2 ? fc(6) : 0.0;
+        Gf[T2][T2] = a2 ? fc(7) : 0.0;
         const double div = Gf[0][0] + Gf[1][1] + Gf[2][2];
         double work = 0.0;
 #pragma unroll
@@ -169,145 +216,116 @@ __device__ __forceinline__ void visc_point_flux(const double *__restrict__ U, co
         }
         F[NS + 3] = work;
     }
-    if (terms & kViscousHeat) F[NS + 3] = F[NS + 3] + fc(Q + C) * nd(P);     // - q_c = kappa dT/dx
-    if (terms & kViscousDiffusion) {
-        double rho[4], Tm[4], rinv[4];
+    if (face && heat) F[NS + 3] = F[NS + 3] + fc(8) * nd(9);     // - q_c = kappa dT/dx
+    if (diff) {
+        if (face) {
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            double r = 0.0;
-#pragma unroll
-            for (int s = 0; s < NS; ++s) r += U[s * C + c[m]];
-            rho[m] = r;
-            rinv[m] = P[3 * C + c[m]];
-            Tm[m] = P[c[m]];
+            for (int s = 0; s < NS; ++s) hf[s] = fc(10 + s);
         }
-        const double rf = fv_face(rho[0], rho[1], rho[2], rho[3]);
-        double Yf[NS], Df[NS], dY[NS];
-        double corr = 0.0;
+        __syncthreads();
+        S[0][t] = rho;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            double y[4];
-#pragma unroll
-            for (int m = 0; m < 4; ++m) y[m] = U[s * C + c[m]] * rinv[m];
-            Yf[s] = fv_face(y[0], y[1], y[2], y[3]);
-            dY[s] = fv_normal(y[0], y[1], y[2], y[3], i24h);
-            Df[s] = fc(Q + (5 + s) * C);
-            corr = corr + Df[s] * dY[s];
+            S[1 + s][t] = y[s];
+            S[1 + NS + s][t] = D[s];
         }
-        double e = F[NS + 3];
+        __syncthreads();
+        if (face) {
+            const double rf = fc(0);
+            double Yf[NS], Dd[NS];
+            double corr = 0.0;
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const double J = -rf * (Df[s] * dY[s] - Yf[s] * corr);
-            F[s] = -J;
-            double hm[4];
+            for (int s = 0; s < NS; ++s) {
+                Yf[s] = fc(1 + s);
+                Dd[s] = fc(1 + NS + s) * nd(1 + s);
+                corr = corr + Dd[s];
+            }
+            double e = F[NS + 3];
 #pragma unroll
-            for (int m = 0; m < 4; ++m) hm[m] = e_species(th, s, Tm[m]) + th.Rs[s] * Tm[m];
-            e = e - fv_face(hm[0], hm[1], hm[2], hm[3]) * J;                     // - q_d
+            for (int s = 0; s < NS; ++s) {
+                const double J = -rf * (Dd[s] - Yf[s] * corr);
+                F[s] = -J;
+                e = e - hf[s] * J;              // - q_d
+            }
+            F[NS + 3] = e;
         }
-        F[NS + 3] = e;
+    }
+    double r[NV];
+    if (fin) {
+#pragma unroll
+        for (int q = 0; q < NV; ++q) r[q] = rhs[q * C + cell];
+    }
+    __syncthreads();
+    if (face) {
+#pragma unroll
+        for (int q = 0; q < NV; ++q) S[q][t] = F[q];
+    }
+    __syncthreads();
+    if (fin) {
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+            const double hl = (-S[q][t - 3 * W] + 26.0 * S[q][t - 2 * W] - S[q][t - W]) * (1.0 / 24.0);
+            const double hr = (-S[q][t - 2 * W] + 26.0 * S[q][t - W] - S[q][t]) * (1.0 / 24.0);
+            rhs[q * C + cell] = r[q] + (hr - hl) * id;
+        }
     }
 }
 
 // ---------------------------------------------------------------------------
-// x direction: point faces k = -1..nx+1 of every interior row, linearised
-// (nx + 3 per row); a block of 256 threads takes 256 consecutive faces and
-// blocks overlap by three, so each cell's four point faces meet in one block.
-// The block count is a multiple of the XCD count and each XCD takes one
-// contiguous range of faces (neighbouring blocks share their edge cells in
-// one L2).
-// The point fluxes go to LDS; a thread whose face closes a cell's window
-// (the cell's last point face) adds that cell's residual.
+// x direction: cells -3..nx+2 of every interior row, linearised (nx + 6 per
+// row); a block of 256 threads takes 256 consecutive cells and blocks overlap
+// by six, so each cell's four point faces meet in one block.  The block count
+// is a multiple of the XCD count and each XCD takes one contiguous range of
+// cells (neighbouring blocks share their edge cells in one L2).
 // ---------------------------------------------------------------------------
 constexpr int kViscXBlock = 256;
 
-// Both viscous face kernels ask for at least five waves per SIMD: the
-// compiler's default of four left them latency-bound (at nine species the x
-// kernel then keeps 96 registers with a few dozen bytes of spill, the tile
-// kernel 80 registers with none, which gives it six).
 template <int NS>
-__global__ __launch_bounds__(kViscXBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_visc_x(const double *__restrict__ U, const double *__restrict__ P,
-                                                       const double *__restrict__ Q, const double *__restrict__ G,
-                                                       double *__restrict__ rhs, Geo g, ThermoK<double> th,
-                                                       int terms) {
-    constexpr int NV = NS + 4;
-    __shared__ double sF[NV][kViscXBlock];
+__global__ __launch_bounds__(kViscXBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_visc_x(
+    const double *__restrict__ U, const double *__restrict__ P, const double *__restrict__ Q,
+    const double *__restrict__ G, double *__restrict__ rhs, Geo g, ThermoK<double> th, int terms) {
+    __shared__ double S[ViscStage<NS>::kFields][kViscXBlock];
     unsigned lb, u1, u2;
     xcd_block(lb, u1, u2);
     const int t = threadIdx.x;
-    const long long per_row = (long long)g.nx + 3;
-    const long long nfaces = per_row * g.ny * g.nz;
-    const long long f0 = (long long)lb * (kViscXBlock - 3);
-    if (f0 >= nfaces) return;   // blocks that round the grid up to a multiple of 8
+    const long long n = ((long long)g.nx + 6) * g.ny * g.nz;
+    const long long f0 = (long long)lb * (kViscXBlock - 6);
+    if (f0 >= n) return;   // blocks that round the grid up to a multiple of 8
     const long long f = f0 + t;
-    const bool valid = f < nfaces;
-    long long rowbase = 0;
-    int kk = 0;
-    if (valid) {
-        int j, k;                                // point face k = kk - 1, between cells kk - 2 and kk - 1
-        split3(g, f, g.nx + 3, g.ny, g.dvf, g.dny, kk, j, k);
-        rowbase = (long long)(g.gz + k) * g.sz + (long long)(g.gy + j) * g.sy + g.gx;
-        double F[NV];
-        visc_point_flux<NS, 0>(U, P, Q, G, rowbase + kk - 3, 1, g, th, g.idx / 24.0, terms, F);
-#pragma unroll
-        for (int q = 0; q < NV; ++q) sF[q][t] = F[q];
-    }
-    __syncthreads();
-    if (valid && t >= 3 && kk >= 3) {
-        const long long cell = rowbase + kk - 3;
-#pragma unroll
-        for (int q = 0; q < NV; ++q) {
-            const double hl = (-sF[q][t - 3] + 26.0 * sF[q][t - 2] - sF[q][t - 1]) * (1.0 / 24.0);
-            const double hr = (-sF[q][t - 2] + 26.0 * sF[q][t - 1] - sF[q][t]) * (1.0 / 24.0);
-            rhs[q * g.cells + cell] += (hr - hl) * g.idx;
-        }
-    }
+    int kk, j, k;                                // cell kk - 3 of row (j, k)
+    split3(g, f < n ? f : n - 1, g.nx + 6, g.ny, g.dvf, g.dny, kk, j, k);
+    const long long cell = (long long)(g.gz + k) * g.sz + (long long)(g.gy + j) * g.sy + g.gx + kk - 3;
+    const bool face = f < n && kk <= g.nx + 2 && t < kViscXBlock - 3;
+    visc_block<NS, 0, kViscXBlock, 1>(U, P, Q, G, rhs, g, th, terms, g.idx, S, t, cell, face,
+                                      face && kk >= 3 && t >= 3);
 }
 
 // ---------------------------------------------------------------------------
-// y/z directions: tiles of 16 x-columns by 16 consecutive point faces along
-// the sweep axis; tiles overlap by three faces, so each finishes 13 cells per
-// column.  Lanes run along x (coalesced loads).
+// y/z directions: tiles of kViscTX x-columns by kViscTS consecutive cells
+// along the sweep axis; tiles overlap by six cells.  Lanes run along x
+// (coalesced loads).
 // ---------------------------------------------------------------------------
-constexpr int kViscTX = 16, kViscTS = 16;
+constexpr int kViscTX = 16, kViscTS = 32;
 
 template <int NS, int DIR>
-__global__ __launch_bounds__(kViscTX *kViscTS) __attribute__((amdgpu_waves_per_eu(5))) void k_visc_tile(const double *__restrict__ U,
-                                                               const double *__restrict__ P,
-                                                               const double *__restrict__ Q,
-                                                               const double *__restrict__ G,
-                                                               double *__restrict__ rhs, Geo g,
-                                                               ThermoK<double> th, int terms) {
-    constexpr int NV = NS + 4;
-    __shared__ double sF[NV][kViscTS][kViscTX];
+__global__ __launch_bounds__(kViscTX *kViscTS) __attribute__((amdgpu_waves_per_eu(4))) void k_visc_tile(
+    const double *__restrict__ U, const double *__restrict__ P, const double *__restrict__ Q,
+    const double *__restrict__ G, double *__restrict__ rhs, Geo g, ThermoK<double> th, int terms) {
+    __shared__ double S[ViscStage<NS>::kFields][kViscTX * kViscTS];
     unsigned bx, by, bz;
     xcd_block(bx, by, bz);
     const int tx = threadIdx.x, ts = threadIdx.y;
     const int x = bx * kViscTX + tx;
-    const int kk = by * (kViscTS - 3) + ts;       // point face k = kk - 1
+    const int kk = by * (kViscTS - 6) + ts;       // cell kk - 3 of the column
     const int nsw = DIR == 1 ? g.ny : g.nz;
-    const bool valid = x < g.nx && kk <= nsw + 2;
-    const long long step = DIR == 1 ? g.sy : g.sz;
-    const int gs = DIR == 1 ? g.gy : g.gz;
-    const long long col = (long long)(g.gx + x) +
-                          (DIR == 1 ? (long long)(g.gz + bz) * g.sz : (long long)(g.gy + bz) * g.sy);
-    const double id = DIR == 1 ? g.idy : g.idz;
-    if (valid) {
-        double F[NV];
-        visc_point_flux<NS, DIR>(U, P, Q, G, col + (long long)(gs + kk - 3) * step, step, g, th, id / 24.0, terms,
-                                 F);
-#pragma unroll
-        for (int q = 0; q < NV; ++q) sF[q][ts][tx] = F[q];
-    }
-    __syncthreads();
-    if (valid && ts >= 3) {
-        const long long cell = col + (long long)(gs + kk - 3) * step;
-#pragma unroll
-        for (int q = 0; q < NV; ++q) {
-            const double hl = (-sF[q][ts - 3][tx] + 26.0 * sF[q][ts - 2][tx] - sF[q][ts - 1][tx]) * (1.0 / 24.0);
-            const double hr = (-sF[q][ts - 2][tx] + 26.0 * sF[q][ts - 1][tx] - sF[q][ts][tx]) * (1.0 / 24.0);
-            rhs[q * g.cells + cell] += (hr - hl) * id;
-        }
-    }
+    const long long col =
+        (long long)(g.gx + min(x, g.nx - 1)) +
+        (DIR == 1 ? (long long)(g.gz + bz) * g.sz : (long long)(g.gy + bz) * g.sy);
+    const long long cell =
+        col + (long long)((DIR == 1 ? g.gy : g.gz) + min(kk, nsw + 5) - 3) * (DIR == 1 ? g.sy : g.sz);
+    const bool face = x < g.nx && kk <= nsw + 2 && ts < kViscTS - 3;
+    visc_block<NS, DIR, kViscTX * kViscTS, kViscTX>(U, P, Q, G, rhs, g, th, terms, DIR == 1 ? g.idy : g.idz, S,
+                                                    ts * kViscTX + tx, cell, face, face && ts >= 3);
 }
 
 }  // namespace xf
