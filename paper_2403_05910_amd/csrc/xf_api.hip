@@ -243,13 +243,25 @@ int viscous_into(xf_ctx *c, const double *U, const Prim &pb, double *const out[3
     return XF_OK;
 }
 
-// Where a primitive pass puts the GLF speeds (zeroed here), or null for the
-// other artificial viscosities.
-hipError_t glf_target(xf_ctx *c, unsigned long long *mx, unsigned long long **to, hipStream_t s) {
-    *to = nullptr;
-    if (c->lc.visc != XF_VISC_GLF) return hipSuccess;
-    *to = mx + 1;
-    return timed(c, XF_K_CFL, s, [&] { return xf::launch_reset_u64(mx + 1, 9, s); });
+// Where a primitive pass puts the GLF speeds, or null for the other artificial
+// viscosities; zeroed here, and with cfl the CFL maximum and the block count too.
+hipError_t glf_target(xf_ctx *c, unsigned long long *mx, unsigned long long **to, hipStream_t s, bool cfl = false) {
+    *to = c->lc.visc == XF_VISC_GLF ? mx + 1 : nullptr;
+    if (!cfl && !*to) return hipSuccess;
+    return timed(c, XF_K_CFL, s, [&] {
+        return cfl ? xf::launch_reset_u64(mx, xf::kCflDone + 1, s) : xf::launch_reset_u64(mx + 1, 9, s);
+    });
+}
+
+// *dt = cfl / the CFL maximum (Eq. 17) of U, by a primitive pass that keeps
+// only the maximum
+int cfl_into(xf_ctx *c, const double *U, double cfl, double *dt, unsigned long long *mx, hipStream_t s) {
+    XF_TRY(timed(c, XF_K_CFL, s, [&] { return xf::launch_reset_u64(mx, 1, s); }));
+    XF_TRY(timed(c, XF_K_PRIMS, s, [&] {
+        return c->ops->prims(c->lc, U, nullptr, nullptr, nullptr, 0, nullptr, xf::CflArgs{mx}, nullptr, s);
+    }));
+    XF_TRY(timed(c, XF_K_CFL, s, [&] { return xf::launch_cfl_finish(mx, cfl, dt, s); }));
+    return XF_OK;
 }
 
 const double *glf_of(const xf_ctx *c, const unsigned long long *mx, int d) {
@@ -258,11 +270,11 @@ const double *glf_of(const xf_ctx *c, const unsigned long long *mx, int d) {
 
 // p64 = false: the FP64 primitives are not needed (the FP32 copies are).
 // Ug = U: the pass also fills the ghosts of U it covers.  cfl: the pass also
-// takes the CFL maximum into *cfl (zeroed beforehand)
+// takes the CFL maximum
 hipError_t prims(xf_ctx *c, const double *U, const Prim &pb, hipStream_t s, bool p64 = true, double *Ug = nullptr,
-                 unsigned long long *cfl = nullptr) {
+                 const xf::CflArgs &cfl = {}) {
     unsigned long long *glf;
-    const hipError_t e = glf_target(c, pb.mx, &glf, s);
+    const hipError_t e = glf_target(c, pb.mx, &glf, s, cfl.mx != nullptr);
     if (e != hipSuccess) return e;
     // viscous contexts: every padded cell (the tangential derivatives read edge ghosts)
     return timed(c, XF_K_PRIMS, s, [&] {
@@ -371,7 +383,7 @@ int rhs_vjp_into(xf_ctx *c, const double *U, const double *rbar, double *Ubar, d
     unsigned long long *glf;
     XF_TRY(glf_target(c, mx, &glf, s));
     XF_TRY(timed(c, XF_K_PRIMS, s,
-                 [&] { return c->ops->prims(lc, U, P, nullptr, nullptr, 0, nullptr, nullptr, glf, s); }));
+                 [&] { return c->ops->prims(lc, U, P, nullptr, nullptr, 0, nullptr, {}, glf, s); }));
     XF_TRY(timed(c, XF_K_ZERO, s, [&] { return xf::launch_zero(3 * lc.g.cells, Pbar, s); }));
     for (int d = 0; d < 3; ++d) {
         if (n[d] <= 1) continue;
@@ -669,7 +681,7 @@ int xf_rhs_alpha(xf_ctx *c, const double *U, const double *alpha_in, double *alp
 int xf_primitives(xf_ctx *c, const double *U, double *prim, void *stream) {
     if (!c || !U || !prim || !aligned8(U) || !aligned8(prim)) return XF_EINVAL;
     const hipStream_t s = (hipStream_t)stream;
-    XF_TRY(timed(c, XF_K_PRIMS, s, [&] { return c->ops->prims(c->lc, U, prim, nullptr, nullptr, 1, nullptr, nullptr, nullptr, s); }));
+    XF_TRY(timed(c, XF_K_PRIMS, s, [&] { return c->ops->prims(c->lc, U, prim, nullptr, nullptr, 1, nullptr, {}, nullptr, s); }));
     return XF_OK;
 }
 
@@ -677,21 +689,13 @@ int xf_cfl_dt(xf_ctx *c, const double *U, double cfl, double *dt_dev, void *ws, 
     if (!c || !U || !dt_dev || !ws || !(cfl > 0.0) || !aligned8(U) || !aligned8(ws)) return XF_EINVAL;
     const Layout l = layout(c, XF_OP_RHS);
     const hipStream_t s = (hipStream_t)stream;
-    double *P = at<double>(ws, l.P);
-    unsigned long long *mx = at<unsigned long long>(ws, l.mx);
-    XF_TRY(timed(c, XF_K_PRIMS, s, [&] { return c->ops->prims(c->lc, U, P, nullptr, nullptr, 0, nullptr, nullptr, nullptr, s); }));
-    XF_TRY(timed(c, XF_K_CFL, s, [&] {
-        hipError_t e = xf::launch_cfl_reset(mx, s);
-        if (e == hipSuccess) e = c->ops->cfl(c->lc, U, P, mx, s);
-        if (e == hipSuccess) e = xf::launch_cfl_finish(mx, cfl, dt_dev, s);
-        return e;
-    }));
-    return XF_OK;
+    return cfl_into(c, U, cfl, dt_dev, at<unsigned long long>(ws, l.mx), s);
 }
 
 // One SSP-RK3 step (ping-pong stage buffers S1, S2; stage 3 writes U in
-// place).  With cfl > 0 the time step is reduced on the device from the stage-1 primitives of U^n and
-// written to *dt_out before it is used.
+// place).  With cfl > 0 the time step is reduced on the device from the stage-1
+// primitives of U^n and written to *dt_out before it is used.
+constexpr long long kCflInPass = 1 << 13;   // padded cells (32 blocks)
 int flow_rk3_step(xf_ctx *c, double *U, double dt, const double *dt_in, double cfl, double *dt_out, void *ws,
                   hipStream_t s);
 
@@ -712,15 +716,9 @@ int rk3_step(xf_ctx *c, double *U, double dt, const double *dt_in, double cfl, d
     const double *h = dt_in;
     if (cfl > 0.0) {
         const Layout l = layout(c, XF_OP_RK3);
-        const Prim pb = prim_bufs(c, l, ws);
         XF_TRY(fill(c, U, s));
-        XF_TRY(prims(c, U, pb, s));
-        XF_TRY(timed(c, XF_K_CFL, s, [&] {
-            hipError_t e = xf::launch_cfl_reset(pb.mx, s);
-            if (e == hipSuccess) e = c->ops->cfl(c->lc, U, pb.P, pb.mx, s);
-            if (e == hipSuccess) e = xf::launch_cfl_finish(pb.mx, cfl, dt_out, s);
-            return e;
-        }));
+        const int r = cfl_into(c, U, cfl, dt_out, at<unsigned long long>(ws, l.mx), s);
+        if (r != XF_OK) return r;
         h = dt_out;
     }
     int r;
@@ -740,7 +738,6 @@ int flow_rk3_step(xf_ctx *c, double *U, double dt, const double *dt_in, double c
     double *S1 = at<double>(ws, l.U0), *S2 = at<double>(ws, l.S2);
     double *L = mixed ? nullptr : at<double>(ws, l.L);
     double *Lv = mixed && c->viscous ? at<double>(ws, l.Lv) : nullptr;
-    unsigned long long *mx = pb.mx;
     const double *h = dt_in;
     double *in[3] = {U, S1, S2};
     double *out[3] = {S1, S2, U};
@@ -756,12 +753,14 @@ int flow_rk3_step(xf_ctx *c, double *U, double dt, const double *dt_in, double c
     // the CFL maximum of U^n (Eq. 17) is taken by the first primitive pass
     for (int k = 0; k < 3; ++k) {
         const bool take_cfl = k == 0 && cfl > 0.0;
-        if (take_cfl) XF_TRY(timed(c, XF_K_CFL, s, [&] { return xf::launch_cfl_reset(mx, s); }));
-        XF_TRY(prims(c, in[k], pb, s, p64, in[k], take_cfl ? mx : nullptr));
-        if (take_cfl) {
-            XF_TRY(timed(c, XF_K_CFL, s, [&] { return xf::launch_cfl_finish(mx, cfl, dt_out, s); }));
-            h = dt_out;
-        }
+        // one count a block and a division by the last: cheaper than a launch
+        // while the blocks are few (600 cells: a step 40.9 -> 37.9 us; with 107
+        // blocks 73.5 -> 74.0, each block waiting for its own maximum)
+        const bool within = take_cfl && lc.g.cells <= kCflInPass;
+        XF_TRY(prims(c, in[k], pb, s, p64, in[k],
+                     {take_cfl ? pb.mx : nullptr, cfl, within ? dt_out : nullptr}));
+        if (take_cfl && !within) XF_TRY(timed(c, XF_K_CFL, s, [&] { return xf::launch_cfl_finish(pb.mx, cfl, dt_out, s); }));
+        if (take_cfl) h = dt_out;
         const int r = stage_into(c, in[k], out[k], U, a[k], b[k], dt, h, pb, L, Lv, s);
         if (r != XF_OK) return r;
     }

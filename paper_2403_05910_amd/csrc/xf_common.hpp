@@ -166,6 +166,17 @@ struct StageArgs {
     double a = 0.0, b = 1.0;
 };
 
+// Where a primitive pass takes the CFL maximum max_i sum_d (|u_d| + c) / dx_d
+// (Eq. 17): into mx[0], as the bits of a double.  With dt set the pass's last
+// block also writes *dt = cfl / maximum, mx[kCflDone] counting the blocks done.
+// Both are zeroed beforehand.
+constexpr int kCflDone = 10;   // after the nine GLF speeds
+struct CflArgs {
+    unsigned long long *mx = nullptr;
+    double cfl = 0.0;
+    double *dt = nullptr;
+};
+
 // Everything a launch needs besides buffers.
 struct LaunchCtx {
     Geo g;
@@ -185,13 +196,12 @@ struct NsOps {
     // the pass covers are filled on the way, each from its boundary source as
     // the ghost fill does (without all_cells: the face ghosts; the edge and
     // corner ghosts lie outside every stencil and are left)
-    // With cfl, the pass also folds the CFL rate of its interior cells
-    // (Eq. 17, as the cfl entry) into *cfl, which the caller has zeroed.
+    // With cfl.mx, the pass also folds the CFL rate of its interior cells into it.
     // With glf, the GLF speeds of the active directions, the largest |u_d - c|,
     // |u_d|, |u_d + c| over every cell direction d's stencils read, into
     // glf[3 d .. 3 d + 2] (uint64 bits of positive doubles; zeroed beforehand).
     hipError_t (*prims)(const LaunchCtx &, const double *U, double *P, float *Uf, float *Pf, int all_cells,
-                        double *Ug, unsigned long long *cfl, unsigned long long *glf, hipStream_t);
+                        double *Ug, const CflArgs &cfl, unsigned long long *glf, hipStream_t);
     // one direction of the convective flux difference.  FP64 sweeps read U,
     // P and write rhs (accumulate: rhs +=, else rhs =); mixed-precision
     // sweeps read Uf, Pf and write the FP32 differences to rhs32 (no
@@ -217,9 +227,6 @@ struct NsOps {
     // VJP of the primitive map: Ubar += (d(p, T, rho)/dU)^T Pbar
     hipError_t (*prims_vjp)(const LaunchCtx &, const double *U, const double *P,
                             const double *Pbar, double *Ubar, hipStream_t);
-    // CFL reduction: max_i sum_d (|u_d| + c)/dx_d -> atomicMax on *mx (uint64 bits)
-    hipError_t (*cfl)(const LaunchCtx &, const double *U, const double *P,
-                      unsigned long long *mx, hipStream_t);
     // transport pass at every padded cell: Q[transport_fields(ns)][cells]
     hipError_t (*transport)(const LaunchCtx &, const double *U, const double *P, double *Q, const TransportK *tk,
                             hipStream_t);
@@ -272,7 +279,6 @@ hipError_t launch_rk3_stage_vjp(const LaunchCtx &, int nv, int stage, double *la
 // a mixed context, summed in FP64 in the order of the FP64 sweeps; null for
 // an inactive direction)
 hipError_t launch_sum_dirs(const LaunchCtx &, int nv, double *rhs, const float *const L[3], hipStream_t);
-hipError_t launch_cfl_reset(unsigned long long *mx, hipStream_t);
 // cell-centred velocity gradient from the velocity fields Q[2..4] of the
 // transport pass: G[3 a + b][cells], fourth-order differences along every
 // active axis a at the cells two or more layers inside the padded extent

@@ -1,9 +1,9 @@
 // xf_forward.hpp -- forward kernels of the convective right-hand side.
 //
-//   k_prims       primitive recovery with the Newton temperature (Eq. 7, 21)
+//   k_prims       primitive recovery with the Newton temperature (Eq. 7, 21);
+//                 the CFL maximum (Eq. 17) and the GLF speeds
 //   k_sweep_x     x-direction flux difference, one face per thread
 //   k_sweep_tile  y/z-direction flux difference, tiles of one face per thread
-//   k_cfl         CFL reduction (Eq. 17), wavefront max + one 64-bit atomic
 #pragma once
 
 #include "xf_face64.hpp"
@@ -132,11 +132,14 @@ __device__ __forceinline__ unsigned cell_prims(const Get &u, const ThermoK<doubl
 // Uf, Pf (optional): FP32 copies of U and of (T, p, c, 1/rho) for the
 // mixed-precision sweeps, written for the same cells; P may be null when
 // only they are needed.
-template <int NS>
+// DT: the last block also divides.  With a run-time switch instead, the passes
+// that do not divide got slower (a CU6 GLF right-hand side of 0.7 M cells 268 ->
+// 271 us).
+template <int NS, bool DT>
 __global__ __launch_bounds__(256) void k_prims(const double *U, double *__restrict__ P, Geo g,
                                                ThermoK<double> th, unsigned *status, float *__restrict__ Uf,
                                                float *__restrict__ Pf, int all_cells, double *Ug,
-                                               unsigned long long *cfl, unsigned long long *glf) {
+                                               unsigned long long *mx, unsigned long long *glf, double cfl, double *dt) {
     const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     // with glf: the direction's speeds |u_d - c|, |u_d|, |u_d + c| of a cell its
     // stencils read (interior in the other axes)
@@ -191,7 +194,7 @@ __global__ __launch_bounds__(256) void k_prims(const double *U, double *__restri
                 Pf[2 * C + idx] = (float)c;
                 Pf[3 * C + idx] = (float)rinv;
             }
-            if (cfl && ng == 0) {   // the same sum, in the same order, as k_cfl
+            if (mx && ng == 0) {
                 double v = 0.0;
                 if (g.nx > 1) v += (fabs(u[NS] * rinv) + c) * g.idx;
                 if (g.ny > 1) v += (fabs(u[NS + 1] * rinv) + c) * g.idy;
@@ -237,7 +240,7 @@ __global__ __launch_bounds__(256) void k_prims(const double *U, double *__restri
             if (bits > __atomic_load_n(glf + threadIdx.x, __ATOMIC_RELAXED)) atomicMax(glf + threadIdx.x, bits);
         }
     }
-    if (cfl) {
+    if (mx) {
         // block max, then one 64-bit atomicMax (positive doubles order like
         // their bit patterns), skipped when the running max is already larger
 #pragma unroll
@@ -248,7 +251,14 @@ __global__ __launch_bounds__(256) void k_prims(const double *U, double *__restri
         if (threadIdx.x == 0) {
             const double m = fmax(fmax(wmax[0], wmax[1]), fmax(wmax[2], wmax[3]));
             const unsigned long long bits = (unsigned long long)__double_as_longlong(m);
-            if (bits > __atomic_load_n(cfl, __ATOMIC_RELAXED)) atomicMax(cfl, bits);
+            if (bits > __atomic_load_n(mx, __ATOMIC_RELAXED)) atomicMax(mx, bits);
+            if constexpr (DT) {
+                __threadfence();
+                if (atomicAdd(mx + kCflDone, 1ull) == gridDim.x - 1) {
+                    __threadfence();
+                    *dt = cfl / __longlong_as_double((long long)atomicMax(mx, 0ull));
+                }
+            }
         }
     }
 }
@@ -747,38 +757,6 @@ k_sweep_tile(const S *__restrict__ U, const S *__restrict__ P, R *__restrict__ r
             },
             [&](int q) { return (double)stage[q * TSZ + (ts + RAD - 1) * kTileX + tx]; });
     if (flags) atomicOr(status, flags);
-}
-
-// ---------------------------------------------------------------------------
-// CFL: max over interior cells of sum_d (|u_d| + c) / dx_d; positive doubles
-// order like their bit patterns, so the max is one 64-bit atomicMax per wave.
-// ---------------------------------------------------------------------------
-template <int NS>
-__global__ __launch_bounds__(256) void k_cfl(const double *__restrict__ U, const double *__restrict__ P, Geo g,
-                                             unsigned long long *mx) {
-    const long long n = (long long)g.nx * g.ny * g.nz;
-    double s = 0.0;
-    for (long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x; q < n;
-         q += (long long)gridDim.x * blockDim.x) {
-        int i, j, k;
-        split3(g, q, g.nx, g.ny, g.dnx, g.dny, i, j, k);
-        const long long idx = (long long)(g.gz + k) * g.sz + (long long)(g.gy + j) * g.sy + (g.gx + i);
-        const double rinv = P[3 * g.cells + idx], c = P[2 * g.cells + idx];
-        double v = 0.0;
-        if (g.nx > 1) v += (fabs(U[NS * g.cells + idx] * rinv) + c) * g.idx;
-        if (g.ny > 1) v += (fabs(U[(NS + 1) * g.cells + idx] * rinv) + c) * g.idy;
-        if (g.nz > 1) v += (fabs(U[(NS + 2) * g.cells + idx] * rinv) + c) * g.idz;
-        if (v > s) s = v;   // NaN never wins (it is flagged by k_prims)
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s = fmax(s, __shfl_xor(s, off, 64));
-    __shared__ double wmax[4];
-    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const double m = fmax(fmax(wmax[0], wmax[1]), fmax(wmax[2], wmax[3]));
-        atomicMax(mx, (unsigned long long)__double_as_longlong(m));
-    }
 }
 
 }  // namespace xf

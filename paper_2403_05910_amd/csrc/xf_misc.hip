@@ -229,8 +229,6 @@ __global__ __launch_bounds__(256) void k_rk3_stage_vjp(double *lam, double *lam0
     }
 }
 
-__global__ void k_cfl_reset(unsigned long long *mx) { *mx = 0ull; }
-
 __global__ void k_reset_u64(unsigned long long *p, int n) {
     if ((int)threadIdx.x < n) p[threadIdx.x] = 0ull;
 }
@@ -313,11 +311,6 @@ hipError_t launch_sum_dirs(const LaunchCtx &c, int nv, double *rhs, const float 
 
 hipError_t launch_vel_grad(const LaunchCtx &c, const double *Q, double *G, hipStream_t s) {
     hipLaunchKernelGGL(k_vel_grad, dim3(blocks_for(c.g.cells, 256)), dim3(256), 0, s, Q, G, c.g);
-    return hipGetLastError();
-}
-
-hipError_t launch_cfl_reset(unsigned long long *mx, hipStream_t s) {
-    hipLaunchKernelGGL(k_cfl_reset, dim3(1), dim3(1), 0, s, mx);
     return hipGetLastError();
 }
 

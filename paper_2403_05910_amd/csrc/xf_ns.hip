@@ -17,10 +17,16 @@ constexpr int NS = XF_NS;
 unsigned blocks_for(long long n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 
 hipError_t prims(const LaunchCtx &c, const double *U, double *P, float *Uf, float *Pf, int all_cells, double *Ug,
-                 unsigned long long *cfl, unsigned long long *glf, hipStream_t s) {
+                 const CflArgs &cfl, unsigned long long *glf, hipStream_t s) {
     if (Ug && Ug != U) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_prims<NS>, dim3(blocks_for(c.g.cells, 256)), dim3(256), 0, s, U, P, c.g, c.th64,
-                       c.status, Uf, Pf, all_cells, Ug, cfl, glf);
+    if (cfl.dt && !cfl.mx) return hipErrorInvalidValue;
+    const dim3 grid(blocks_for(c.g.cells, 256)), block(256);
+    if (cfl.dt)
+        hipLaunchKernelGGL((k_prims<NS, true>), grid, block, 0, s, U, P, c.g, c.th64, c.status, Uf, Pf, all_cells, Ug,
+                           cfl.mx, glf, cfl.cfl, cfl.dt);
+    else
+        hipLaunchKernelGGL((k_prims<NS, false>), grid, block, 0, s, U, P, c.g, c.th64, c.status, Uf, Pf, all_cells, Ug,
+                           cfl.mx, glf, 0.0, nullptr);
     return hipGetLastError();
 }
 
@@ -270,14 +276,6 @@ hipError_t prims_vjp(const LaunchCtx &c, const double *U, const double *P, const
     return hipGetLastError();
 }
 
-hipError_t cfl(const LaunchCtx &c, const double *U, const double *P, unsigned long long *mx, hipStream_t s) {
-    const long long n = (long long)c.g.nx * c.g.ny * c.g.nz;
-    long long nb = blocks_for(n, 256);
-    if (nb > 2048) nb = 2048;   // grid-stride: one atomic per block
-    hipLaunchKernelGGL(k_cfl<NS>, dim3((unsigned)nb), dim3(256), 0, s, U, P, c.g, mx);
-    return hipGetLastError();
-}
-
 hipError_t transport(const LaunchCtx &c, const double *U, const double *P, double *Q, const TransportK *tk,
                      hipStream_t s) {
     hipLaunchKernelGGL(k_transport<NS>, dim3(blocks_for(c.g.cells, 256)), dim3(256), 0, s, U, P, Q, c.g, tk);
@@ -304,7 +302,7 @@ hipError_t viscous(const LaunchCtx &c, int dir, const double *U, const double *P
     return hipGetLastError();
 }
 
-const NsOps kOps = {prims, sweep, sweep_vjp, sweep_frozen, face_speeds, prims_vjp, cfl, transport, viscous, react_launch<NS>,
+const NsOps kOps = {prims, sweep, sweep_vjp, sweep_frozen, face_speeds, prims_vjp, transport, viscous, react_launch<NS>,
                     few32<NS, float>() ? few32_stage : nullptr};
 
 }  // namespace
