@@ -754,7 +754,7 @@ int flow_rk3_step(xf_ctx *c, double *U, double dt, const double *dt_in, double c
     for (int k = 0; k < 3; ++k) {
         const bool take_cfl = k == 0 && cfl > 0.0;
         // one count a block and a division by the last: cheaper than a launch
-        // while the blocks are few (600 cells: a step 40.9 -> 37.9 us; with 107
+        // while the blocks are few (200 cells: a step 40.9 -> 37.9 us; with 107
         // blocks 73.5 -> 74.0, each block waiting for its own maximum)
         const bool within = take_cfl && lc.g.cells <= kCflInPass;
         XF_TRY(prims(c, in[k], pb, s, p64, in[k],
@@ -856,29 +856,29 @@ int xf_set_reactions(xf_ctx *c, const xf_mechanism *m, int substeps, int splitti
             if (!std::isfinite(e) || e < 0.0) return XF_EINVAL;
             h.nf[r][s] = f;
             h.nb[r][s] = b;
-            h.fd[r][s] = f;
-            h.bd[r][s] = b;
+            h.rx[r].fd[s] = f;
+            h.rx[r].bd[s] = b;
             for (int k = 0; k < f; ++k) {
-                const unsigned n = h.fl[r] & 7u;
+                const unsigned n = h.rx[r].fl & 7u;
                 if (n == 7u) return XF_EINVAL;   // more than seven reactant molecules
-                h.fl[r] = (h.fl[r] + 1u) | ((unsigned)s << (3 + 4 * n));
+                h.rx[r].fl = (h.rx[r].fl + 1u) | ((unsigned)s << (3 + 4 * n));
             }
             for (int k = 0; k < b; ++k) {
-                const unsigned n = h.bl[r] & 7u;
+                const unsigned n = h.rx[r].bl & 7u;
                 if (n == 7u) return XF_EINVAL;   // more than seven product molecules
-                h.bl[r] = (h.bl[r] + 1u) | ((unsigned)s << (3 + 4 * n));
+                h.rx[r].bl = (h.rx[r].bl + 1u) | ((unsigned)s << (3 + 4 * n));
             }
-            h.eff[r][s] = e;
+            h.rx[r].eff[s] = e;
             dn += b - f;
             dm += c->W[s] * (b - f);
         }
         if (std::fabs(dm) > 1e-9 * wmax) return XF_EINVAL;   // the reaction must conserve mass
-        h.dn[r] = dn;
-        h.third[r] = m->third[r];
-        h.rev[r] = m->reversible[r];
-        h.lnA[r] = std::log(m->A[r]);
-        h.B[r] = m->B[r];
-        h.ER[r] = m->E[r] / xf::kRu;
+        h.rx[r].dn = dn;
+        h.rx[r].third = m->third[r];
+        h.rx[r].rev = m->reversible[r];
+        h.rx[r].lnA = std::log(m->A[r]);
+        h.rx[r].B = m->B[r];
+        h.rx[r].ER = m->E[r] / xf::kRu;
     }
     h.th = c->lc.th64;
     h.lp0 = std::log(xf::kP0 / xf::kRu);
@@ -897,7 +897,7 @@ int xf_set_reactions(xf_ctx *c, const xf_mechanism *m, int substeps, int splitti
                 const int nu = h.nb[r][s] - h.nf[r][s];
                 if (nu) acc += nu * (k < 6 ? c->a[s][k] : m->s0[s]);
             }
-            h.G[r][k] = acc * kGibbs[k];
+            h.rx[r].G[k] = acc * kGibbs[k];
         }
     if (!c->rk && hipMalloc(reinterpret_cast<void **>(&c->rk), sizeof(xf::ReactK)) != hipSuccess) {
         c->rk = nullptr;

@@ -128,21 +128,21 @@ constexpr int kMaxReactions = XF_MAX_REACTIONS;
 struct ReactK {
     int nr;
     int nf[kMaxReactions][kMaxNs], nb[kMaxReactions][kMaxNs];
-    int dn[kMaxReactions];          // sum_s (nu'' - nu')
-    int third[kMaxReactions], rev[kMaxReactions];
-    double lnA[kMaxReactions], B[kMaxReactions], ER[kMaxReactions];
-    double eff[kMaxReactions][kMaxNs];
-    // sum_s (nu'' - nu') g_s(T), with g_s = S_s/R_s - h_s/(R_s T) linear in the
-    // species' NASA coefficients, folded per reaction:
-    // dg = G0 (ln T - 1) + G1 T + G2 T^2 + G3 T^3 + G4 T^4 + G5 / T + G6
-    double G[kMaxReactions][7];
+    // what a rate evaluation reads of one reaction, in the order it reads it
+    struct Rx {
+        double lnA, B, ER, dn;   // dn = sum_s (nu'' - nu')
+        // the reactant and product lists (the count in bits 0..2, then up to
+        // seven species indices of four bits each, a species listed nu times)
+        unsigned fl, bl;
+        int third, rev;
+        double eff[kMaxNs];
+        double fd[kMaxNs], bd[kMaxNs];   // nu' and nu'' for the accumulation of q and p
+        // sum_s (nu'' - nu') g_s(T), with g_s = S_s/R_s - h_s/(R_s T) linear in
+        // the species' NASA coefficients, folded per reaction:
+        // dg = G0 (ln T - 1) + G1 T + G2 T^2 + G3 T^3 + G4 T^4 + G5 / T + G6
+        double G[7];
+    } rx[kMaxReactions];
     double W[kMaxNs], iW[kMaxNs];
-    // per reaction, for scalar loads ahead of the species work: the reactant
-    // and product lists (the count in bits 0..2, then up to seven species
-    // indices of four bits each, a species listed nu times), and nu' and
-    // nu'' as doubles for the accumulation of q and p
-    unsigned fl[kMaxReactions], bl[kMaxReactions];
-    double fd[kMaxReactions][kMaxNs], bd[kMaxReactions][kMaxNs];
     ThermoK<double> th;   // the context's species tables, for the temperature solves
     double lp0;           // ln(p0 / R_u)
 };
