@@ -147,14 +147,16 @@ def roofline_of(kernels, case, precision, workload):
     name = max(sweeps, key=lambda k: kernels[k][0])
     ms, launches = kernels[name]
     avg_s = ms / launches / 1e3
-    # the mixed x sweep of an RK3 step (no viscous terms or blend) also
-    # finishes the stage
-    fused = precision == "mixed" and name == "sweep_x"
+    # the last active sweep of an RK3 step finishes the stage; in FP64 every
+    # later one adds to what the earlier ones left
+    last = next(k for k in sweeps if case.n[sweeps[k]] > 1)
+    fused = name == last
+    first = precision == "mixed" or all(case.n[d] <= 1 for d in range(sweeps[name] + 1, 3))
     flops = pm.sweep_flops(ns, case.n, sweeps[name]) + (pm.stage_flops(ns, case.n) if fused else 0)
     achieved = flops / avg_s / 1e12
     peak = pm.PEAK["fp32_vector_TFLOPs" if precision == "mixed" else "fp64_vector_TFLOPs"]
     traffic = measured_traffic(name, precision, workload)
-    alg_bytes = pm.sweep_bytes(ns, case.n, sweeps[name], first=True, precision=precision, fused_stage=fused)
+    alg_bytes = pm.sweep_bytes(ns, case.n, sweeps[name], first=first, precision=precision, fused_stage=fused)
     out = {"kernel": name + (" (with the stage)" if fused else ""), "bound": "alu", "achieved": achieved,
            "peak": peak, "unit": "TFLOP/s",
            "frac": achieved / peak, "traffic": traffic, "traffic_unit": "bytes/launch",

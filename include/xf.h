@@ -358,8 +358,8 @@ enum {
     XF_K_SWEEP_Y = 2,      /* y flux difference                                  */
     XF_K_SWEEP_Z = 3,      /* z flux difference                                  */
     XF_K_FILL = 4,         /* ghost fill (all active directions of one call)     */
-    XF_K_STAGE = 5,        /* SSP-RK3 stage combination                          */
-    XF_K_CFL = 6,          /* CFL reduction                                      */
+    XF_K_STAGE = 5,        /* stages no sweep finishes, buffer sums and copies   */
+    XF_K_CFL = 6,          /* CFL maximum and GLF speeds: zeroing, the division  */
     XF_K_ZERO = 7,         /* zeroing of rhs ghosts / VJP scratch                */
     XF_K_VJP_X = 8,        /* x flux-difference VJP                              */
     XF_K_VJP_Y = 9,

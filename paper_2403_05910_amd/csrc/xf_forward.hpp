@@ -264,24 +264,20 @@ __global__ __launch_bounds__(256) void k_prims(const double *U, double *__restri
 }
 
 // ---------------------------------------------------------------------------
-// Phase fences, loop form and occupancy per kernel flavour, chosen from the
-// compiler's resource report and timings at 256^3, nine species:
-// * the x sweeps run the species loops rolled (face_flux_to ROLL): FP64 at
-//   three waves per SIMD without spill (168 registers; 2.20 -> 2.00 ms per
-//   launch), FP32 1.74 -> 1.33 ms;
-// * the y/z tiles roll their species loops too (their shapes, LDS and
-//   waves per SIMD are at TileShape);
-// * the positivity-blend instances stay at two waves (at three the FP64
-//   blended step went from 37.5 to 47.7 ms), the FP64 WENO7 instances at
-//   one (at two they spilled 324-460 bytes per lane; at one they keep their
-//   overflow in the accumulation registers, 61.7 -> 50.3 ms per step).
+// Occupancy per kernel flavour, from the compiler's resource report and
+// timings at 256^3, nine species: the exchanging FP64 WENO5 instances fit three
+// waves per SIMD (168 registers) without spill, with their species loops rolled
+// two species at a time; the positivity-blend instances stay at two (at three the
+// FP64 blended step went from 37.5 to 47.7 ms, taken with an earlier face), CU6
+// too (28 to 120 bytes of spill at three), the FP64 WENO7 instances at one (at
+// two they spilled 324-460 bytes per lane).
 // Waves per SIMD asked of a face-per-thread sweep (X: the x sweep).
 template <typename R, int REC, bool X, bool PP>
 constexpr int sweep_waves() {
     if (sizeof(R) == 4) return X ? 4 : (!PP && REC == kReconWeno5) ? 5 : 1;
     if (REC == kReconWeno7) return 1;
     if (!X && !PP && REC == kReconWeno5) return 3;     // the exchanging FP64 tiles (CU6 spills at three)
-    return (X && !PP && REC == kReconWeno5) ? 3 : 2;   // the rolled CU6 x face spills ~100 bytes at three
+    return (X && !PP && REC == kReconWeno5) ? 3 : 2;
 }
 
 // lam = D dt / dx_d of the positivity blend (D active dimensions).
@@ -470,7 +466,9 @@ __device__ __forceinline__ StoreOut<Put> store_out(Put p) {
 // the cell below as soon as it is final, taking the neighbouring face's
 // value from the next lane down; the first lane of each wave takes it
 // through LDS.  The others keep the block's fluxes in LDS (the blend limits
-// whole flux vectors).  A mixed RK3 step's x sweep also finishes the stage (sa.Uout).
+// whole flux vectors).  In an RK3 step it also finishes the stage (sa.Uout),
+// which at 256^3 and nine species makes it memory bound: 7.5 GB in FP64, 1.81 ms,
+// where a copy of that size takes 1.72.
 // ---------------------------------------------------------------------------
 constexpr int kXBlock = 256;
 
@@ -490,7 +488,8 @@ inline int x_faces_per_block(long long nfx) {
 
 // Exchanging x sweeps: FP64 WENO5 (three waves per SIMD).  The CU6 and
 // WENO7 faces (two and one waves per SIMD) took 3.09 ms per x sweep
-// exchanging against 2.62 and 2.65 ms with the fluxes in LDS.
+// exchanging against 2.62 and 2.65 ms with the fluxes in LDS (256^3, nine
+// species, with an earlier face).
 template <typename R, int REC, bool PP>
 constexpr bool x_exchange() { return sizeof(R) == 8 && REC == kReconWeno5 && !PP; }
 
@@ -652,11 +651,12 @@ __global__ __launch_bounds__(kXBlock) __attribute__((amdgpu_waves_per_eu(sweep_w
 // registers); the other instances are 16 x 16 with the fluxes in LDS (FP64:
 // 72 KB, two waves; the CU6 and WENO7 faces need more than the 168
 // registers of three waves; FP32: 36 KB, four waves).  Measured at 256^3,
-// nine species, y/z: FP64 WENO5 2.92/3.01 ms unstaged, 2.10/2.19 staged at
-// 16 x 16, 1.92/1.97 exchanging at 8 x 32 (CU6 and WENO7 ran 5 % slower at
-// 8 x 32 than at 16 x 16); FP32 1.43/1.49 unstaged at 32 x 8, 1.36/1.37
-// staged at 32 x 8 or 32 x 16, 1.15/1.16 staged at 16 x 16, 1.12/1.11
-// exchanging at 8 x 32 (1.12/1.12 exchanging at 16 x 16).
+// nine species, y/z, the shapes with an earlier face: FP64 WENO5 2.92/3.01 ms
+// unstaged, 2.10/2.19 staged at 16 x 16, 1.92/1.97 exchanging at 8 x 32 (CU6 and
+// WENO7 ran 5 % slower at 8 x 32 than at 16 x 16); FP32 1.43/1.49 unstaged at
+// 32 x 8, 1.15/1.16 staged at 16 x 16, 1.12/1.11 exchanging at 8 x 32.  With the
+// present faces, in an RK3 step: FP64 1.79 (y, adding to the sum) and 1.52 (z),
+// FP32 1.08/1.09.
 template <typename R, int REC, bool PP>
 struct TileShape {
     static constexpr bool exchange = REC == kReconWeno5 && !PP;

@@ -212,7 +212,7 @@ hipError_t launch_vjp_group(const LaunchCtx &c, const ThermoK<R> &th, int dir, i
         const int W = 69 + 5 * bounds;
         const size_t per_wave = vjp_x_lds_per_wave<NS, R>(W);
         // one wave per block, so the waves of a CU run their staging, faces
-        // and window merge out of step (FP64, with the plain face, 12.3 ->
+        // and window merge out of step (FP64, with an earlier face, 12.3 ->
         // 12.0 ms per direction at 256^3, nine species, against four-wave
         // blocks)
         if (per_wave > kVjpLdsBytes) return hipErrorInvalidValue;
@@ -243,7 +243,7 @@ hipError_t launch_vjp_group(const LaunchCtx &c, const ThermoK<R> &th, int dir, i
 // Two launch groups per direction (x: waves w = grp mod 2; y/z: face
 // blocks b = grp mod 2), one kernel each: neighbours share window cells,
 // next-but-one neighbours none (measured at 256^3, nine species, the RHS VJP
-// took 46.4 ms with six groups and 45.6 ms with two).
+// took 46.4 ms with six groups and 45.6 ms with two, with an earlier face).
 template <typename R>
 hipError_t sweep_vjp_t(const LaunchCtx &c, const ThermoK<R> &th, int dir, const double *U, const double *P,
                        const double *rbar, double *Ubar, double *Pbar, const Dissip &ds, hipStream_t s) {

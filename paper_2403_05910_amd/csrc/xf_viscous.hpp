@@ -30,7 +30,7 @@ namespace xf {
 // a fit f is taken through its root, sqrt(a_s) = exp(f / 2), which the mixing
 // rule needs anyway; divisions are by reciprocals of positive normal numbers.
 // With libm's exp, sqrt and IEEE divisions (3837 vector instructions a wave,
-// now about 2300) this pass and the velocity gradient took 488 us at nine
+// now 2918) this pass and the velocity gradient took 488 us at nine
 // species and 2.9 M cells, now 400 us.
 template <int NS>
 __global__ __launch_bounds__(256) void k_transport(const double *__restrict__ U, const double *__restrict__ P,

@@ -846,13 +846,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(vjp_waves<R
 // (F + 5) x 16 cells and its face cotangents into LDS.
 // ---------------------------------------------------------------------------
 constexpr int kVjpTX = 16, kVjpWin = kVjpTX * 9;
-// Waves per y/z block (four faces each): two in FP64, so that two blocks of
-// 65 KB share a CU and one block's staging and window merge overlap the
-// other's faces (RHS VJP at 256^3, nine species, 45.6 -> 44.8 ms against
-// four-wave blocks of 119 KB, one per CU); four in FP32, whose blocks hold
-// no staged tile (there two-wave blocks measured 35.3 -> 36.2 ms).  Blocks
-// of at least five faces keep next-but-one neighbours disjoint (two launch
-// groups).
+// Waves per y/z block (four faces each): two, so that two FP64 blocks share a
+// CU and one block's staging and window merge overlap the other's faces (RHS
+// VJP at 256^3, nine species, with an earlier face 45.6 -> 44.8 ms against
+// four-wave blocks, one per CU).  Blocks of at least five faces keep
+// next-but-one neighbours disjoint (two launch groups).
 template <typename R>
 constexpr int vjp_yz_waves() { return 2; }
 template <typename R>
@@ -934,7 +932,7 @@ __global__ __launch_bounds__(64 * vjp_yz_waves<R>()) __attribute__((amdgpu_waves
         }
     }
     __syncthreads();
-    // block rows r = 0..20 (sweep rows j0-3 .. j0+17); wave w covers r in [4w, 4w+9)
+    // block rows r = 0..F+4 (sweep rows j0-3 .. j0+F+1); wave w covers r in [4w, 4w+9)
     for (int c = threadIdx.x; c < kVjpTX * kVjpRows; c += 64 * WY) {
         const int r = c / kVjpTX, cx = xi * kVjpTX + (c % kVjpTX);
         const int row = j0 - 3 + r;                       // interior index along the sweep axis

@@ -67,16 +67,16 @@ def sweep_bytes(ns, n, direction, first=True, precision="fp64", fused_stage=Fals
     primitives of every cell its stencils read, once (FP32 copies in the
     mixed path), and the residual of every interior cell written once (read
     as well when accumulated; FP32 differences in the mixed path).  With
-    fused_stage (the mixed x sweep of an RK3 step, which finishes the stage
-    itself) the residual is not written; instead every interior value reads
-    Uin, the other two directions' residuals and, in two of the three
-    stages, U0, and writes Uout (FP64 state)"""
+    fused_stage (the x sweep of an RK3 step, which finishes the stage) the
+    residual is not written; instead every interior value reads the other two
+    directions' sum (mixed: Uin and their two FP32 residuals) and, in two of
+    the three stages, U0, and writes Uout (FP64 state)"""
     nv = ns + 4
     cells = n[0] * n[1] * n[2]
     word = 4 if precision == "mixed" else 8
     stencil = word * (nv + 4) * _footprint(n, direction)
     if fused_stage:
-        return stencil + nv * cells * (8 + 2 * word + 8 + 8 * 2 / 3)
+        return stencil + nv * cells * ((16 if precision == "mixed" else 8) + 8 + 8 * 2 / 3)
     return stencil + (word if first else 2 * word) * nv * cells
 
 
@@ -108,14 +108,14 @@ def vjp_sweep_bytes(ns, n, direction):
 # type over the group's faces (profiles/vjp_nine_species_sbi_256.md; the
 # y/z figure from the group whose grid holds no idle threads).  Measured at
 # nine species only: other species counts return None.
-VJP_FACE_OPS = {("fp64", 9): (10178, 10226, 10226), ("mixed", 9): (10324, 10360, 10360)}
+VJP_FACE_OPS = {("fp64", 9): (6937, 6985, 6985), ("mixed", 9): (10365, 10360, 10360)}
 
 # Operations per face of the forward sweeps as executed, counted the same way
-# (x sweep, nine species): FP64 3985, FP32 4155 -- about 19 % above the
-# algorithmic count F(9) = 3360 of face_flops, for the divide and square-root
-# sequences (counted once in F) and the rolled species loops, which
-# evaluate e_s(T~) three times per species.
-EXECUTED_FACE_OPS = {("fp64", 9): 3985, ("mixed", 9): 4155}
+# (x sweep, nine species), against the algorithmic count F(9) = 3360 of
+# face_flops: the FP64 face works on first differences and shared sums; the FP32
+# one keeps the plain forms and executes more (divide and square-root
+# sequences, counted once in F, and species thermo evaluated three times).
+EXECUTED_FACE_OPS = {("fp64", 9): 3080, ("mixed", 9): 4150}
 
 
 def vjp_face_flops(ns, precision="fp64", direction=0):
@@ -132,8 +132,8 @@ def vjp_sweep_flops(ns, n, direction, precision="fp64"):
 
 
 def rk3_step_bytes_per_cell(ns):
-    """one fused-free RK3 step, algorithmic: 3 x (RHS read U + write L) plus
-    3 stage updates (read U^n, U^(k-1), L; write U^(k))"""
+    """one RK3 step in separate passes, algorithmic: 3 x (RHS read U + write
+    L) plus 3 stage updates (read U^n, U^(k-1), L; write U^(k))"""
     nv = ns + 4
     return 3 * 16 * nv + 3 * 32 * nv
 
