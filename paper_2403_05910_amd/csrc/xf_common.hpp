@@ -268,6 +268,16 @@ inline long long face_count(const Geo &g, int d) {
 // one z-plane, launch groups of every second wave, blocks of up to 4 waves.
 constexpr int kVjpGroups = 2;
 inline long long vjp_x_waves_per_plane(const Geo &g) { return ((long long)(g.nx + 1) * g.ny + 63) / 64; }
+// The cells a wave's faces touch: stencil cell 0 of face f of a z-plane,
+// counted from the padded start of the plane's first interior row, and the
+// longest run, of 64 faces (their first cells, the row ends they cross, where
+// the first cells of neighbouring faces lie 2 gx - 1 cells further apart, and
+// the last face's other five).
+__host__ __device__ inline long long vjp_x_first(const Geo &g, long long f) {
+    const long long rowf = (long long)g.nx + 1, r = f / rowf;
+    return r * g.sy + (g.gx - 3) + (f - r * rowf);
+}
+inline int vjp_x_run(const Geo &g) { return 69 + (2 * g.gx - 1) * ((63 + g.nx) / (g.nx + 1)); }
 
 // Species-independent launches (xf_misc.hip).
 hipError_t launch_fill_ghosts(const LaunchCtx &, int nv, double *U, hipStream_t);

@@ -207,9 +207,7 @@ hipError_t launch_vjp_group(const LaunchCtx &c, const ThermoK<R> &th, int dir, i
     const Geo &g = c.g;
     if (dir == 0) {
         // consecutive faces per wave with private LDS areas of W cells
-        const int rowf = g.nx + 1;
-        const int bounds = (63 + rowf - 1) / rowf;               // row boundaries 64 faces can cross
-        const int W = 69 + 5 * bounds;
+        const int W = vjp_x_run(g);
         const size_t per_wave = vjp_x_lds_per_wave<NS, R>(W);
         // one wave per block, so the waves of a CU run their staging, faces
         // and window merge out of step (FP64, with an earlier face, 12.3 ->

@@ -741,12 +741,13 @@ struct VjpMerge {
 // x direction: lanes take consecutive x faces, linearised over the rows of
 // one z-plane (face f of the plane: row f / (nx + 1), face f % (nx + 1)).
 // The padded rows of a plane are contiguous, so the cells the 64 faces of a
-// wave touch form one run of at most W = 69 + 5 b padded cells (b = row
-// boundaries the wave crosses; face k of the wave has its stencil at offset
-// k + 5 b_k).  Each wave accumulates its cotangents in a private LDS window
-// over that run: within one instruction the 64 lanes address 64 distinct
-// cells, and the window accesses keep program order, so no atomics are
-// needed.  The window is then added to Ubar / Pbar with coalesced
+// wave touch form one run of at most W = 69 + (2 gx - 1) b padded cells (b =
+// row boundaries the wave crosses; face k of the wave has its stencil at
+// offset k + (2 gx - 1) b_k; gx = 3 or 4).  Each wave accumulates its
+// cotangents in a private LDS window over that run: within one instruction the
+// 64 lanes address 64 distinct cells, and the window accesses keep program
+// order, so no atomics are needed.  The window is then added to Ubar / Pbar
+// with coalesced
 // read-modify-writes.  Runs of waves w and w + 1 can share up to five cells,
 // those of w and w + 2 cannot; launch `grp` takes the waves w = grp mod 2.
 // The run's U and primitives and the faces' cotangents go to private LDS
@@ -778,14 +779,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(vjp_waves<R
     R *tile = (R *)(w + (size_t)NW * W);
     R *bars = tile + (size_t)NT * W;
     const long long f0 = wid * 64, f = f0 + lane;
-    const long long r0 = f0 / rowf;
-    const long long base0 = zb + r0 * g.sy + (f0 - r0 * rowf);   // stencil cell 0 of the wave's first face
-    int span = 0;                                                 // cells of the wave's run
-    if (wid < wpp) {
-        const long long fl = min(f0 + 63, nfp - 1);
-        const long long rl = fl / rowf;
-        span = (int)(zb + rl * g.sy + (fl - rl * rowf) - base0) + 6;
-    }
+    const long long base0 = zb + vjp_x_first(g, f0);     // stencil cell 0 of the wave's first face
+    int span = 0;                                        // cells of the wave's run
+    if (wid < wpp) span = (int)(zb + vjp_x_first(g, min(f0 + 63, nfp - 1)) - base0) + 6;
     for (int i = lane; i < NW * W; i += 64) w[i] = 0.0;
     // this lane's face: face i of row r of the plane
     const bool mine = wid < wpp && f < nfp;
