@@ -1,6 +1,8 @@
 // xf_misc.hip -- species-independent kernels: boundary ghosts and their
 // adjoint, ghost zeroing, SSP-RK3 stage combinations (Eq. 16) and their
 // adjoint, CFL finish, copies.
+#include <algorithm>
+
 #include "xf_common.hpp"
 
 namespace xf {
@@ -98,88 +100,119 @@ struct Shell {
     __host__ __device__ int cell(int k) const { return k < lo ? k : hi + (k - lo); }
 };
 
-__host__ __device__ __forceinline__ long long shell_count(const Geo &g) {
-    const Shell x(g.nx, g.gx), y(g.ny, g.gy), z(g.nz, g.gz);
-    return (long long)z.count() * g.nx * g.ny + (long long)z.inner() * ((long long)y.count() * g.nx +
+// What one launch folds: per axis its cells from padded index org on, and the
+// ghost layers folded onto them (0: none along this axis).
+struct Fold {
+    int n[3], ng[3], org[3];
+};
+
+__host__ __device__ __forceinline__ long long shell_count(const Fold &g) {
+    const Shell x(g.n[0], g.ng[0]), y(g.n[1], g.ng[1]), z(g.n[2], g.ng[2]);
+    return (long long)z.count() * g.n[0] * g.n[1] + (long long)z.inner() * ((long long)y.count() * g.n[0] +
            (long long)y.inner() * x.count());
 }
 
-// The padded positions along one axis that hold copies of interior cell c:
-// itself (k = 0) and its ghost images (k = 1 .. count - 1).
+// The padded positions along one axis that hold interior cell c or a copy of
+// it, as offsets from it: lo, lo + step, ..., count of them (periodic: a period
+// apart; outflow: the end cell and the layers outside it).
 struct Images {
-    int self, first, stride, count;
-    __device__ Images(int c, int n, int ng, int lo, int hi) : self(ng + c), first(0), stride(1), count(1) {
+    int lo, step, count;
+    __device__ Images(int c, int n, int ng, int bc) : lo(0), step(1), count(1) {
         if (ng == 0) return;
-        if (lo == XF_BC_PERIODIC) {   // periodic sides come in pairs
-            const bool below = c >= n - ng, above = c < ng;
-            first = below ? self - n : self + n;
-            stride = 2 * n;
+        const bool below = c >= n - ng, above = c < ng;   // copies below and above it
+        if (bc == XF_BC_PERIODIC) {   // periodic sides come in pairs
+            lo = below ? -n : 0;
+            step = n;
             count = 1 + below + above;
-        } else {
-            if (c == 0) {
-                count += ng;
-            } else if (c == n - 1) {
-                first = ng + n;
-                count += ng;
-            }
+        } else if (c == 0 || c == n - 1) {
+            lo = c == 0 ? -ng : 0;
+            count = 1 + ng;
         }
-        (void)hi;
     }
-    __device__ int at(int k) const { return k == 0 ? self : first + (k - 1) * stride; }
 };
 
-// (Against a launch per axis, each behind the one before: 125 -> 78 us at
-// 176 x 144 x 128, nine species, 29 -> 16 us at 64^3, five species.)
-__global__ __launch_bounds__(256) void k_fill_vjp(double *Ub, Geo g, int nv) {
+// One thread per cell with copies and kFillFields fields.  On small grids the
+// time is that of the thread with the most copies, one chain of loads: next to an
+// outflow side a cell holds all NG layers, NG + 1 values, the square of that at an
+// edge and the cube at a corner.  So NG + 1 values (a row of copies; all a face
+// cell holds) are asked for at once, without a branch between the loads, the next
+// one's address takes additions only, and the launch below folds z apart where
+// two axes have outflow sides.  64^3, five species, three layers: periodic 8.3 us,
+// outflow 15.6 (the loads one by one, each behind a zero store: 12.0 and 43.4;
+// an axis per launch 23.9 and 22.4); 256^3, nine species, outflow: 143 (225, 335).
+template <int NG>
+__global__ __launch_bounds__(256) void k_fill_vjp(double *Ub, Geo g, Fold fo, int nv) {
     long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= shell_count(g)) return;
-    const Shell sx(g.nx, g.gx), sy(g.ny, g.gy), sz(g.nz, g.gz);
+    if (q >= shell_count(fo)) return;
+    const Shell sx(fo.n[0], fo.ng[0]), sy(fo.n[1], fo.ng[1]), sz(fo.n[2], fo.ng[2]);
+    const int nx = fo.n[0];
     int i, j, k;
-    const long long plane = (long long)g.nx * g.ny;
+    const long long plane = (long long)nx * fo.n[1];
     if (q < sz.count() * plane) {
         const int m = (int)(q / plane);
         const long long r = q - m * plane;
         k = sz.cell(m);
-        j = (int)(r / g.nx);
-        i = (int)(r - (long long)j * g.nx);
+        j = (int)(r / nx);
+        i = (int)(r - (long long)j * nx);
     } else {
         q -= sz.count() * plane;
-        const long long slab = (long long)sy.count() * g.nx + (long long)sy.inner() * sx.count();
+        const long long slab = (long long)sy.count() * nx + (long long)sy.inner() * sx.count();
         const int m = (int)(q / slab);
         long long r = q - m * slab;
         k = sz.lo + m;
-        if (r < (long long)sy.count() * g.nx) {
-            const int e = (int)(r / g.nx);
+        if (r < (long long)sy.count() * nx) {
+            const int e = (int)(r / nx);
             j = sy.cell(e);
-            i = (int)(r - (long long)e * g.nx);
+            i = (int)(r - (long long)e * nx);
         } else {
-            r -= (long long)sy.count() * g.nx;
+            r -= (long long)sy.count() * nx;
             const int e = (int)(r / sx.count());
             j = sy.lo + e;
             i = sx.cell((int)(r - (long long)e * sx.count()));
         }
     }
-    const Images X(i, g.nx, g.gx, g.bc[0], g.bc[1]), Y(j, g.ny, g.gy, g.bc[2], g.bc[3]),
-        Z(k, g.nz, g.gz, g.bc[4], g.bc[5]);
-    if (X.count * Y.count * Z.count == 1) return;
-    const int f0 = blockIdx.y * kFillFields;
-    double *u = Ub + f0 * g.cells;
+    const Images X(i, nx, fo.ng[0], g.bc[0]), Y(j, fo.n[1], fo.ng[1], g.bc[2]), Z(k, fo.n[2], fo.ng[2], g.bc[4]);
+    const int n = X.count * Y.count * Z.count;
+    if (n == 1) return;
+    const int f0 = blockIdx.y * kFillFields, last = min(kFillFields, nv - f0) - 1;
+    double *u = Ub + f0 * g.cells + (fo.org[0] + i) + g.sy * (fo.org[1] + j) + g.sz * (fo.org[2] + k);
+    // the image at hand, x fastest: its numbers in x and y and its offset
+    const long long o0 = X.lo + g.sy * Y.lo + g.sz * Z.lo;
+    const long long dx = X.step, dy = g.sy * Y.step - dx * X.count, dz = g.sz * Z.step - g.sy * Y.step * Y.count;
+    int a = 0, b = 0;
+    long long o = o0;
+    auto next = [&] {
+        const bool wx = ++a == X.count;
+        a = wx ? 0 : a;
+        b += wx;
+        const bool wy = b == Y.count;
+        b = wy ? 0 : b;
+        o += dx + (wx ? dy : 0) + (wy ? dz : 0);
+    };
     double v[kFillFields] = {};
-    for (int c = 0; c < Z.count; ++c)
-        for (int b = 0; b < Y.count; ++b)
-            for (int a = 0; a < X.count; ++a) {
-                const long long o = X.at(a) + g.sy * Y.at(b) + g.sz * Z.at(c);
+    for (int m = 0; m < n; m += NG + 1) {
+        // past the last image the cell itself is read, past the last field the
+        // last one; neither is added
+        double w[NG + 1][kFillFields];
 #pragma unroll
-                for (int f = 0; f < kFillFields; ++f)
-                    if (f0 + f < nv) {
-                        v[f] += u[f * g.cells + o];
-                        if (a + b + c > 0) u[f * g.cells + o] = 0.0;
-                    }
-            }
-    const long long o = X.self + g.sy * Y.self + g.sz * Z.self;
+        for (int t = 0; t <= NG; ++t) {
+            const double *p = u + (m + t < n ? o : 0);
 #pragma unroll
-    for (int f = 0; f < kFillFields; ++f)
-        if (f0 + f < nv) u[f * g.cells + o] = v[f];
+            for (int f = 0; f < kFillFields; ++f) w[t][f] = p[min(f, last) * g.cells];
+            next();
+        }
+#pragma unroll
+        for (int t = 0; t <= NG; ++t)
+#pragma unroll
+            for (int f = 0; f < kFillFields; ++f) v[f] += m + t < n ? w[t][f] : 0.0;
+    }
+    a = b = 0;
+    o = o0;
+    for (int m = 0; m < n; ++m, next()) {
+#pragma unroll
+        for (int f = 0; f < kFillFields; ++f)
+            if (f <= last) u[f * g.cells + o] = o == 0 ? v[f] : 0.0;
+    }
 }
 
 // rhs = ((Lz + Ly) + Lx) on the interior cells from FP32 per-direction
@@ -285,8 +318,33 @@ hipError_t launch_fill_ghosts(const LaunchCtx &c, int nv, double *U, hipStream_t
 }
 
 hipError_t launch_fill_ghosts_vjp(const LaunchCtx &c, int nv, double *Ub, hipStream_t s) {
-    hipLaunchKernelGGL(k_fill_vjp, dim3(blocks_for(shell_count(c.g), 256), field_groups(nv)), dim3(256), 0, s, Ub, c.g, nv);
-    return hipGetLastError();
+    const Geo &g = c.g;
+    const int n[3] = {g.nx, g.ny, g.nz}, ng[3] = {g.gx, g.gy, g.gz}, p[3] = {g.px, g.py, g.pz};
+    // folds the axes of a bit set, onto the padded extent of those left for a
+    // later launch
+    auto fold = [&](int axes, int later) {
+        Fold f;
+        for (int d = 0; d < 3; ++d) {
+            const bool whole = later >> d & 1;
+            f.n[d] = whole ? p[d] : n[d];
+            f.ng[d] = axes >> d & 1 ? ng[d] : 0;
+            f.org[d] = whole ? 0 : ng[d];
+        }
+        const dim3 grid(blocks_for(shell_count(f), 256), field_groups(nv));
+        if (std::max(std::max(ng[0], ng[1]), ng[2]) <= 3)
+            hipLaunchKernelGGL(k_fill_vjp<3>, grid, dim3(256), 0, s, Ub, g, f, nv);
+        else
+            hipLaunchKernelGGL(k_fill_vjp<4>, grid, dim3(256), 0, s, Ub, g, f, nv);
+        return hipGetLastError();
+    };
+    // two or three axes with outflow sides: z first, in a launch of its own (one
+    // launch for all: 64^3 with two, three layers 16.2 against 10.9 us, four layers
+    // 23.2 against 12.4)
+    int outflow = 0;
+    for (int d = 0; d < 3; ++d) outflow += ng[d] > 0 && g.bc[2 * d] != XF_BC_PERIODIC;
+    if (outflow < 2 || ng[2] == 0 || ng[0] * ng[1] == 0) return fold(7, 0);
+    const hipError_t e = fold(4, 3);
+    return e == hipSuccess ? fold(3, 0) : e;
 }
 
 hipError_t launch_zero_ghosts(const LaunchCtx &c, int nv, double *A, hipStream_t s) {
