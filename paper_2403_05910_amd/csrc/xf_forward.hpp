@@ -132,18 +132,20 @@ __device__ __forceinline__ unsigned cell_prims(const Get &u, const ThermoK<doubl
 // Uf, Pf (optional): FP32 copies of U and of (T, p, c, 1/rho) for the
 // mixed-precision sweeps, written for the same cells; P may be null when
 // only they are needed.
-// DT: the last block also divides.  With a run-time switch instead, the passes
-// that do not divide got slower (a CU6 GLF right-hand side of 0.7 M cells 268 ->
-// 271 us).
-template <int NS, bool DT>
+// DT: the last block also divides; GLF: the pass takes the GLF speeds.  With
+// run-time switches instead, the passes that do neither got slower: with DT, a
+// CU6 GLF right-hand side of 0.7 M cells took 271 us instead of 268; with GLF,
+// the pass alone 13.7 us instead of 13.1 (64^3, nine species) and 43.5 instead of
+// 42.0 (128^3, five).
+template <int NS, bool DT, bool GLF>
 __global__ __launch_bounds__(256) void k_prims(const double *U, double *__restrict__ P, Geo g,
                                                ThermoK<double> th, unsigned *status, float *__restrict__ Uf,
                                                float *__restrict__ Pf, int all_cells, double *Ug,
                                                unsigned long long *mx, unsigned long long *glf, double cfl, double *dt) {
     const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    // with glf: the direction's speeds |u_d - c|, |u_d|, |u_d + c| of a cell its
+    // GLF: the direction's speeds |u_d - c|, |u_d|, |u_d + c| of a cell its
     // stencils read (interior in the other axes)
-    double gv[9] = {};
+    double gv[GLF ? 9 : 1] = {};
     double sv = 0.0;   // with cfl: the cell's rate sum_d (|u_d| + c) / dx_d of Eq. 17 (interior cells)
     if (idx < g.cells) {
         int x, y, z;
@@ -201,7 +203,7 @@ __global__ __launch_bounds__(256) void k_prims(const double *U, double *__restri
                 if (g.nz > 1) v += (fabs(u[NS + 2] * rinv) + c) * g.idz;
                 if (v > sv) sv = v;   // NaN never wins (it is flagged)
             }
-            if (glf) {
+            if constexpr (GLF) {
                 const bool in[3] = {x >= g.gx && x < g.gx + g.nx, y >= g.gy && y < g.gy + g.ny,
                                     z >= g.gz && z < g.gz + g.nz};
                 const bool active[3] = {g.nx > 1, g.ny > 1, g.nz > 1};
@@ -218,7 +220,7 @@ __global__ __launch_bounds__(256) void k_prims(const double *U, double *__restri
             if (flags) atomicOr(status, flags);
         }
     }
-    if (glf) {
+    if constexpr (GLF) {
         // block maxima, then one 64-bit atomicMax each (see below).  A pass of
         // its own per direction read the state again, 27 us each at 0.7 M
         // cells where the primitives themselves take 21

@@ -21,12 +21,16 @@ hipError_t prims(const LaunchCtx &c, const double *U, double *P, float *Uf, floa
     if (Ug && Ug != U) return hipErrorInvalidValue;
     if (cfl.dt && !cfl.mx) return hipErrorInvalidValue;
     const dim3 grid(blocks_for(c.g.cells, 256)), block(256);
+    auto launch = [&](auto dt, auto speeds) {
+        hipLaunchKernelGGL((k_prims<NS, decltype(dt)::value, decltype(speeds)::value>), grid, block, 0, s, U, P, c.g, c.th64,
+                           c.status, Uf, Pf, all_cells, Ug, cfl.mx, glf, cfl.cfl, cfl.dt);
+    };
+    using No = std::false_type;
+    using Yes = std::true_type;
     if (cfl.dt)
-        hipLaunchKernelGGL((k_prims<NS, true>), grid, block, 0, s, U, P, c.g, c.th64, c.status, Uf, Pf, all_cells, Ug,
-                           cfl.mx, glf, cfl.cfl, cfl.dt);
+        glf ? launch(Yes{}, Yes{}) : launch(Yes{}, No{});
     else
-        hipLaunchKernelGGL((k_prims<NS, false>), grid, block, 0, s, U, P, c.g, c.th64, c.status, Uf, Pf, all_cells, Ug,
-                           cfl.mx, glf, 0.0, nullptr);
+        glf ? launch(No{}, Yes{}) : launch(No{}, No{});
     return hipGetLastError();
 }
 
