@@ -679,9 +679,13 @@ k_sweep_tile(const S *__restrict__ U, const S *__restrict__ P, R *__restrict__ r
     // final, the neighbouring face's value taken across lanes (the face
     // below is kTileX lanes down in the same wave); only the first and last
     // face rows of each wave pass theirs through LDS, for the cell between
-    // two waves.  Otherwise (the blend, which limits the whole flux vector
-    // at once) the fluxes wait in LDS for the block.
-    constexpr bool EXCH = Shape::exchange;
+    // two waves.  Otherwise (the blend, which limits the whole flux vector at
+    // once, and the FP32 sweep that finishes a stage, whose face asks for nothing
+    // ahead: each component then waited out the latency of its own loads) the
+    // fluxes wait in LDS for the block.  A mixed step of nine species without an x
+    // axis, exchanging and not: 300 cells 121 and 111 us, 1200 x 1000 4.14 and 3.97
+    // ms (five species 91 and 83 us, 2.94 and 2.68 ms).
+    constexpr bool EXCH = Shape::exchange && !(sizeof(R) == 4 && MODE == kFinish);
     constexpr int RPW = 64 / kTileX;                   // face rows per wave
     constexpr int NWV = kTileS / RPW;                  // waves per block
     __shared__ R sF[EXCH ? 1 : NV][EXCH ? 1 : kTileS][EXCH ? 1 : kTileX];
