@@ -232,22 +232,27 @@ struct FaceBarLoad {
             for (int q = 0; q < NV; ++q) l[q] = rbar[q * C + cl];
         }
     }
-    // into t[q * 64 + lane]; returns whether any component is nonzero
+    // into t[q * 64 + lane]
     template <typename R>
-    __device__ __forceinline__ bool keep(R *t, int lane, double id) const {
-        bool any = false;
+    __device__ __forceinline__ void keep(R *t, int lane, double id) const {
 #pragma unroll
-        for (int q = 0; q < NV; ++q) {
-            const double d = (r[q] - l[q]) * id;
-            any |= d != 0.0;
-            t[q * 64 + lane] = R(d);
-        }
-        return any;
+        for (int q = 0; q < NV; ++q) t[q * 64 + lane] = R((r[q] - l[q]) * id);
+    }
+    // whether any component is nonzero
+    __device__ __forceinline__ bool any(double id) const {
+        bool a = false;
+#pragma unroll
+        for (int q = 0; q < NV; ++q) a |= (r[q] - l[q]) * id != 0.0;
+        return a;
     }
 };
 // The same read from memory where it is used, and the stencil with it: the
 // FP32 face of a single species, whose loops the compiler takes apart and
-// rounds differently in other surroundings (see xf_few32.hpp).
+// rounds differently in other surroundings (see xf_few32.hpp).  Its y/z blocks
+// stage all the same, which brings the lines they read later close: without, an
+// adjoint of 97 x 90 x 83 cells took 640 us instead of 572.  In x, where a wave's
+// lanes share their lines, staging only delays: 200 cells 42.1 -> 40.5 us,
+// 97 x 90 x 83 573 -> 566, 160 x 160 x 128 (2.28 -> 2.30 ms) the one loss.
 template <int NS, typename R>
 constexpr bool vjp_from_memory() { return sizeof(R) == 4 && NS == 1; }
 struct FaceBarMem {
@@ -757,7 +762,8 @@ struct VjpMerge {
 template <int NS, typename R>
 constexpr size_t vjp_x_lds_per_wave(int W) {
     constexpr size_t NV = NS + 4;
-    return ((NV + kSinkExtra) * W * sizeof(double) + ((NV + 4) * W + NV * 64) * sizeof(R) + 15) / 16 * 16;
+    const size_t staged = vjp_from_memory<NS, R>() ? 0 : ((NV + 4) * W + NV * 64) * sizeof(R);
+    return ((NV + kSinkExtra) * W * sizeof(double) + staged + 15) / 16 * 16;
 }
 
 template <int NS, typename R, bool CU6>
@@ -767,6 +773,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(vjp_waves<R
     constexpr int NV = NS + 4;
     constexpr int NW = NV + kSinkExtra;                    // window rows
     constexpr int NT = NV + 4;                             // staged rows
+    constexpr bool STAGED = !vjp_from_memory<NS, R>();
     extern __shared__ double xf_win[];
     const int wpb = blockDim.x >> 6, wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const long long rowf = (long long)g.nx + 1;          // faces per row
@@ -790,24 +797,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(vjp_waves<R
     const long long row = zb + r * g.sy + g.gx;             // interior cell 0 of the row
     FaceBarLoad<NV> fl;
     fl.load(rbar, C, row + i, row + i - 1, mine && i < g.nx, mine && i > 0);
-    for (int c = lane; c < span; c += 128) {
-        double a[NT], e[NT];
-        const bool two = c + 64 < span;
-        vjp_load<NV>(U, P, C, base0 + c, a);
-        if (two) vjp_load<NV>(U, P, C, base0 + c + 64, e);
+    if constexpr (STAGED) {
+        for (int c = lane; c < span; c += 128) {
+            double a[NT], e[NT];
+            const bool two = c + 64 < span;
+            vjp_load<NV>(U, P, C, base0 + c, a);
+            if (two) vjp_load<NV>(U, P, C, base0 + c + 64, e);
 #pragma unroll
-        for (int q = 0; q < NT; ++q) tile[q * W + c] = R(a[q]);
-        if (two) {
+            for (int q = 0; q < NT; ++q) tile[q * W + c] = R(a[q]);
+            if (two) {
 #pragma unroll
-            for (int q = 0; q < NT; ++q) tile[q * W + c + 64] = R(e[q]);
+                for (int q = 0; q < NT; ++q) tile[q * W + c + 64] = R(e[q]);
+            }
         }
+        fl.keep(bars, lane, g.idx);
     }
-    const bool any = fl.keep(bars, lane, g.idx);
+    const bool any = fl.any(g.idx);
     __syncthreads();
     if (mine && any) {
         const int off = (int)(row + i - 3 - base0);
         const SinkLds<R> sk{(lds_double *)w, W, off, 1, NV * W};
-        if constexpr (vjp_from_memory<NS, R>()) {
+        if constexpr (!STAGED) {
             const Stencil st{U, P, row + i - 3, 1, C};
             vjp_face<NS, R, 0, CU6>(st, th, FaceBarMem{rbar, C, row + i, row + i - 1, i < g.nx, i > 0, g.idx}, sk, ds);
         } else {
@@ -910,7 +920,8 @@ __global__ __launch_bounds__(64 * vjp_yz_waves<R>()) __attribute__((amdgpu_waves
             for (int q = 0; q < NT; ++q) xf_tile[q * TS + te] = R(e[q]);
         }
     }
-    const bool any = fl.keep(xf_bars[wv], lane, DIR == 1 ? g.idy : g.idz);
+    fl.keep(xf_bars[wv], lane, DIR == 1 ? g.idy : g.idz);
+    const bool any = fl.any(DIR == 1 ? g.idy : g.idz);
     __syncthreads();
     if (mine && any) {
         // window row r of wave w = sweep row j0 + 4w - 3 + r; stencil cell m is row ts + m
