@@ -32,7 +32,9 @@ struct FastDiv {
         m = (unsigned)((((unsigned long long)1 << (31 + l)) + d - 1) / d);
         s = l - 1;
     }
-    __device__ __forceinline__ unsigned of(unsigned n) const { return m ? __umulhi(n, m) >> s : n; }
+    __host__ __device__ __forceinline__ unsigned of(unsigned n) const {
+        return m ? (unsigned)((unsigned long long)n * m >> 32) >> s : n;
+    }
 };
 
 // Geometry of one padded SoA field: x fastest, 3 or 4 ghost layers per active axis.
@@ -53,8 +55,8 @@ struct Geo {
 
 // (x, y, z) of linear index q over extents (a, b, ...), da and db their
 // quotients.
-__device__ __forceinline__ void split3(const Geo &g, long long q, int a, int b, const FastDiv &da, const FastDiv &db, int &x,
-                                       int &y, int &z) {
+__host__ __device__ __forceinline__ void split3(const Geo &g, long long q, int a, int b, const FastDiv &da,
+                                                const FastDiv &db, int &x, int &y, int &z) {
     if (g.small) {
         const unsigned r = da.of((unsigned)q), k = db.of(r);
         x = (int)((unsigned)q - r * a);
