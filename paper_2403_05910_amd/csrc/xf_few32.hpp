@@ -18,12 +18,6 @@ namespace xf {
 template <int NS, typename R>
 constexpr bool few32() { return sizeof(R) == 4 && NS <= 2; }
 
-// The finished difference of one field at one cell.
-template <typename OT>
-__device__ __forceinline__ void put_result(OT *__restrict__ rhs, long long o, double d, int accumulate) {
-    rhs[o] = accumulate ? OT(rhs[o] + d) : OT(d);
-}
-
 // SSP-RK3 stage of Eq. 16 on the interior cells: Uout = a U0 + b (Uin + h L),
 // L = ((Lx + Ly) + Lz) + Lv; a block takes one interior row of one field.
 template <int NS>
@@ -50,7 +44,7 @@ __global__ __launch_bounds__(256) void k_few32_stage(double *Uout, const double 
 // x sweep (as k_sweep_x, the fluxes in LDS): one thread per face.
 template <int NS, bool PP, int SPD, int REC>
 __global__ __launch_bounds__(kXBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_few32_x(
-    const float *__restrict__ U, const float *__restrict__ P, float *__restrict__ rhs, Geo g, ThermoK<float> th, int accumulate,
+    const float *__restrict__ U, const float *__restrict__ P, float *__restrict__ rhs, Geo g, ThermoK<float> th,
     StageArgs sa, unsigned *status, Dissip ds, int fpb) {
     using R = float;
     using S = float;
@@ -109,18 +103,18 @@ __global__ __launch_bounds__(kXBlock) __attribute__((amdgpu_waves_per_eu(4))) vo
     unsigned flags = 0;
     long long rowbase = 0;
     const R id = R(g.idx);
-    // the result of interior cell `cell` from its flux difference L (x part)
+    // the result of interior cell `cell` from its flux difference L (x part); a
+    // stage with the blend or viscous fluxes is left to k_few32_stage
     auto emit = [&](int q, long long cell, double L) {
         const long long o = q * g.cells + cell;
-        if (sa.Uout) {
+        if (!PP && sa.Uout) {
             const double h = sa.dt_dev ? *sa.dt_dev : sa.dt;
             if (sa.Ly32) L = L + (double)sa.Ly32[o];
             if (sa.Lz32) L = L + (double)sa.Lz32[o];
-            if (sa.Lv) L = L + sa.Lv[o];
             const double v = sa.Uin[o] + h * L;
             sa.Uout[o] = sa.a == 0.0 ? sa.b * v : sa.a * sa.U0[o] + sa.b * v;
         } else {
-            put_result(rhs, o, L, accumulate);
+            rhs[o] = R(L);
         }
     };
     if (valid) {
@@ -154,7 +148,7 @@ __global__ __launch_bounds__(kXBlock) __attribute__((amdgpu_waves_per_eu(4))) vo
 template <int NS, int DIR, bool PP, int SPD, int REC>
 __global__ __launch_bounds__((TileShape<float, REC, PP>::x * TileShape<float, REC, PP>::s)) __attribute__((amdgpu_waves_per_eu(1))) void
 k_few32_tile(const float *__restrict__ U, const float *__restrict__ P, float *__restrict__ rhs, Geo g, ThermoK<float> th,
-             int accumulate, StageArgs sa, unsigned *status, Dissip ds) {
+             StageArgs sa, unsigned *status, Dissip ds) {
     using R = float;
     using S = float;
     constexpr int NV = NS + 4;
@@ -217,7 +211,7 @@ k_few32_tile(const float *__restrict__ U, const float *__restrict__ P, float *__
                 auto out = store_out([&](int q, R v) {
                         // face j - 1 of this column, valid wherever face j is
                         const R vb = __shfl_up(v, kTileX);
-                        if (r > 0) put_result(rhs, q * g.cells + below, double((vb - v) * id), accumulate);
+                        if (r > 0) rhs[q * g.cells + below] = (vb - v) * id;
                         if (r == RPW - 1) sEdge[0][w][q][tx] = v;
                         if (r == 0) sEdge[1][w][q][tx] = v;
                 });
@@ -247,15 +241,14 @@ k_few32_tile(const float *__restrict__ U, const float *__restrict__ P, float *__
             const long long cell = col + (long long)(gs + j - 1) * step;
 #pragma unroll
             for (int q = 0; q < NV; ++q)
-                put_result(rhs, q * g.cells + cell, double((sEdge[0][w - 1][q][tx] - sEdge[1][w][q][tx]) * id),
-                           accumulate);
+                rhs[q * g.cells + cell] = (sEdge[0][w - 1][q][tx] - sEdge[1][w][q][tx]) * id;
         }
     } else if (valid && ts > 0) {
         const R id = R((DIR == 1) ? g.idy : g.idz);
         const long long cell = col + (long long)(gs + j - 1) * step;
 #pragma unroll
         for (int q = 0; q < NV; ++q)
-            put_result(rhs, q * g.cells + cell, double((sF[q][ts - 1][tx] - sF[q][ts][tx]) * id), accumulate);
+            rhs[q * g.cells + cell] = (sF[q][ts - 1][tx] - sF[q][ts][tx]) * id;
     }
     if (flags) atomicOr(status, flags);
 }

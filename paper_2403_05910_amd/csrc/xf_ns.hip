@@ -48,8 +48,8 @@ hipError_t launch_face_sweep(const LaunchCtx &c, const ThermoK<R> &th, int dir, 
         // the FP32 x sweep keeps its fluxes in LDS: one instance for all modes
         constexpr int XM = x_exchange<R, REC, PP>() ? MODE : kByArgs;
         if constexpr (few32<NS, R>())
-            hipLaunchKernelGGL((k_few32_x<NS, PP, SPD, REC>), dim3(nb), dim3(kXBlock), 0, s, U, P, rhs, g, th, accumulate,
-                               sa, c.status, ds, fpb);
+            hipLaunchKernelGGL((k_few32_x<NS, PP, SPD, REC>), dim3(nb), dim3(kXBlock), 0, s, U, P, rhs, g, th, sa,
+                               c.status, ds, fpb);
         else {
             FastDiv dw;
             dw.set(nfx + 2 * stencil_radius(REC) - 1);
@@ -69,8 +69,8 @@ hipError_t launch_face_sweep(const LaunchCtx &c, const ThermoK<R> &th, int dir, 
     auto tile = [&](auto d) {
         constexpr int DIR = decltype(d)::value;
         if constexpr (few32<NS, R>())
-            hipLaunchKernelGGL((k_few32_tile<NS, DIR, PP, SPD, REC>), grid, block, 0, s, U, P, rhs, g, th, accumulate, sa,
-                               c.status, ds);
+            hipLaunchKernelGGL((k_few32_tile<NS, DIR, PP, SPD, REC>), grid, block, 0, s, U, P, rhs, g, th, sa, c.status,
+                               ds);
         else
             hipLaunchKernelGGL((k_sweep_tile<NS, R, DIR, S, PP, SPD, REC, MODE>), grid, block, 0, s, U, P, rhs, g, th,
                                accumulate, sa, c.status, ds, dgx, dgy);
@@ -88,8 +88,8 @@ template <typename R, typename S, bool PP, int SPD, int REC>
 hipError_t face_sweep_mode(const LaunchCtx &c, const ThermoK<R> &th, int dir, int accumulate, const S *U, const S *P,
                            R *rhs, const StageArgs &sa, const Dissip &ds, hipStream_t s) {
     if constexpr (few32<NS, R>()) {
-        // only the x sweep finishes a stage here
-        if (sa.Uout && dir != 0) return hipErrorInvalidValue;
+        // only the plain x sweep finishes a stage here
+        if (sa.Uout && (PP || dir != 0 || sa.Lv)) return hipErrorInvalidValue;
         return launch_face_sweep<R, S, PP, SPD, REC, kByArgs>(c, th, dir, accumulate, U, P, rhs, sa, ds, s);
     } else if constexpr (TileShape<R, REC, PP>::exchange) {
         if constexpr (SPD != kViscFrozen) {

@@ -64,9 +64,6 @@ XF_HD R weno5_bwd(R a, R b, R c, R d, R e, R hb, R &ab, R &bb, R &cb, R &db, R &
     return W;
 }
 
-// Forward and backward of h = W(g+_{0..4}) + W(g-_{5..1}) with
-// g+- = (wF +- al wU)/2: returns h and the cotangents of wF and wU at the six
-// stencil cells for the output cotangent hb.
 // WENO-CU6 backward (forms as in weno_cu6 of the face code).  Adds
 // hb * dW/d(a..f) to (ab..fb), W the value of weno_cu6(a..f):
 // W = sum_k w_k q_k, w_k = alpha_k / S, alpha_k = d_k (C + tau / e_k),
@@ -161,6 +158,9 @@ XF_HD R split_cu6_fb(const R *gp, const R *gm, R al, R hb, R *wFb, R *wUb) {
     return h;
 }
 
+// Forward and backward of h = W(g+_{0..4}) + W(g-_{5..1}) with
+// g+- = (wF +- al wU)/2: returns h and the cotangents of wF and wU at the six
+// stencil cells for the output cotangent hb.
 template <typename R>
 XF_HD R split_weno_fb(const R *gp, const R *gm, R al, R hb, R *wFb, R *wUb) {
     R pb[6] = {R(0), R(0), R(0), R(0), R(0), R(0)};
@@ -752,11 +752,10 @@ struct VjpMerge {
 // cotangents in a private LDS window over that run: within one instruction the
 // 64 lanes address 64 distinct cells, and the window accesses keep program
 // order, so no atomics are needed.  The window is then added to Ubar / Pbar
-// with coalesced
-// read-modify-writes.  Runs of waves w and w + 1 can share up to five cells,
-// those of w and w + 2 cannot; launch `grp` takes the waves w = grp mod 2.
-// The run's U and primitives and the faces' cotangents go to private LDS
-// areas behind the window, of (NV + 4) W and 64 NV values.
+// with coalesced read-modify-writes.  Runs of waves w and w + 1 can share up to
+// five cells, those of w and w + 2 cannot; launch `grp` takes the waves
+// w = grp mod 2.  The run's U and primitives and the faces' cotangents go to
+// private LDS areas behind the window, of (NV + 4) W and 64 NV values.
 // ---------------------------------------------------------------------------
 // LDS bytes per wave of k_face_vjp_x for a run of W cells.
 template <int NS, typename R>
@@ -767,7 +766,7 @@ constexpr size_t vjp_x_lds_per_wave(int W) {
 }
 
 template <int NS, typename R, bool CU6>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(vjp_waves<R>()))) void k_face_vjp_x(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(vjp_waves<R>()))) void k_face_vjp_x(
     const double *__restrict__ U, const double *__restrict__ P, const double *__restrict__ rbar,
     double *__restrict__ Ubar, double *__restrict__ Pbar, Geo g, ThermoK<R> th, int W, int grp, Dissip ds) {
     constexpr int NV = NS + 4;
@@ -775,14 +774,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(vjp_waves<R
     constexpr int NT = NV + 4;                             // staged rows
     constexpr bool STAGED = !vjp_from_memory<NS, R>();
     extern __shared__ double xf_win[];
-    const int wpb = blockDim.x >> 6, wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int lane = threadIdx.x;                        // a block is one wave
     const long long rowf = (long long)g.nx + 1;          // faces per row
     const long long nfp = rowf * g.ny;                   // faces per plane
     const long long wpp = (nfp + 63) / 64;               // waves per plane
-    const long long wid = kVjpGroups * ((long long)blockIdx.x * wpb + wv) + grp;
+    const long long wid = (long long)kVjpGroups * blockIdx.x + grp;
     const long long C = g.cells;
     const long long zb = (long long)(g.gz + blockIdx.y) * g.sz + (long long)g.gy * g.sy;   // plane's first row
-    double *w = xf_win + (size_t)wv * (vjp_x_lds_per_wave<NS, R>(W) / sizeof(double));
+    double *w = xf_win;
     R *tile = (R *)(w + (size_t)NW * W);
     R *bars = tile + (size_t)NT * W;
     const long long f0 = wid * 64, f = f0 + lane;
