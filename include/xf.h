@@ -339,8 +339,7 @@ int xf_rhs_vjp(xf_ctx *ctx, const double *U, const double *rhs_bar, double *U_ba
                void *ws, void *stream);
 
 /* Adjoint of xf_fill_ghosts: adds every ghost entry of U_bar onto the
- * interior cell it was copied from (reverse order z, y, x) and zeroes the
- * ghost entries. */
+ * interior cell it was copied from and zeroes the ghost entries. */
 int xf_fill_ghosts_vjp(xf_ctx *ctx, double *U_bar, void *stream);
 
 /* Adjoint of one xf_rk3_step with a fixed dt: given U_n (the state before

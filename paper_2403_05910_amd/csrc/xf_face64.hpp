@@ -2,9 +2,10 @@
 // eigenvectors are those at the top of xf_face.hpp; the mixed path's FP32
 // faces keep the forms there).
 //
-// What bounds it: the FP64 sweeps issue vector instructions on about four
-// fifths of the SIMDs' cycles, so the face is written for its instruction
-// count.  Every form below is equal to the plain one in exact arithmetic:
+// What bounds it: in the sweeps that wait least for memory vector instructions
+// issue on two thirds of the SIMDs' cycles (z, which only stores, 67 %; y, which adds
+// to the sum, 57 %; four fifths with the plain forms), so the face is written for its
+// instruction count.  Every form below is equal to the plain one in exact arithmetic:
 //   * the split values g+- = (wF +- alpha wU)/2 are taken times two (times
 //     four in the acoustic fields, where w = DF/2 -+ c XF/(2 c^2) halves once
 //     more) and eps with them; the fluxes leave the face times kFluxScale;

@@ -3,7 +3,7 @@
 // With so few species the compiler takes the species loops of the FP32 face
 // apart and pairs its multiply-adds across them, differently with every
 // change of the code around the face; another pairing is another rounding,
-// and the state moves by 1e-8.  These contexts keep the sweeps and the
+// and the state moves in the eighth digit.  These contexts keep the sweeps and the
 // separate stage kernel whose results they have always had.  From three
 // species on the loops stay loops, the face rounds alike in every kernel, and
 // the sweeps of xf_forward.hpp serve both precisions (1.12 -> 1.07 ms per y/z

@@ -3,8 +3,8 @@
 // For one face, face_vjp recomputes the forward flux of xf_face.hpp and then
 // runs it backwards, given the cotangent Fb of F^_{i+1/2}.  It adds the
 // cotangents of the six stencil cells' conservative values (directly, and
-// through 1/rho = 1/sum_s rho_s) and of the cells' pressure and temperature
-// (into a separate two-field buffer; the per-cell map (p, T)(U) is
+// through 1/rho = 1/sum_s rho_s) and of the cells' pressure, temperature and
+// density (into a separate three-field buffer; the per-cell maps are
 // differentiated afterwards by k_prims_vjp).  The LLF speeds alpha are held
 // fixed.  Every step of the forward is differentiated: back-projection,
 // WENO5-JS weights (through the smoothness indicators), the characteristic
@@ -701,7 +701,7 @@ __device__ __forceinline__ void vjp_face(const St &st, const ThermoK<R> &th, con
 
 // Waves per SIMD the face VJP kernels are compiled for: the FP32 face keeps
 // its state in 256 registers (two waves); the FP64 one needs up to 512 (one
-// wave; at two it spills 744 bytes per lane).  Every block first copies the
+// wave; at two the x kernel spills 572 bytes per lane).  Every block first copies the
 // stencil values of all its faces (U and the primitives, in the face's type)
 // and the face cotangents into LDS, so the face computation waits on no
 // global load.
