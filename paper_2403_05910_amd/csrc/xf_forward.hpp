@@ -136,7 +136,9 @@ __device__ __forceinline__ unsigned cell_prims(const Get &u, const ThermoK<doubl
 // run-time switches instead, the passes that do neither got slower: with DT, a
 // CU6 GLF right-hand side of 0.7 M cells took 271 us instead of 268; with GLF,
 // the pass alone 13.7 us instead of 13.1 (64^3, nine species) and 43.5 instead of
-// 42.0 (128^3, five).
+// 42.0 (128^3, five).  The GLF instance still tests its pointer: without the test
+// its code is scheduled otherwise, and the right-hand side above took 0.5 to 0.8 %
+// longer.
 template <int NS, bool DT, bool GLF>
 __global__ __launch_bounds__(256) void k_prims(const double *U, double *__restrict__ P, Geo g,
                                                ThermoK<double> th, unsigned *status, float *__restrict__ Uf,
@@ -145,7 +147,7 @@ __global__ __launch_bounds__(256) void k_prims(const double *U, double *__restri
     const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     // GLF: the direction's speeds |u_d - c|, |u_d|, |u_d + c| of a cell its
     // stencils read (interior in the other axes)
-    double gv[GLF ? 9 : 1] = {};
+    double gv[9] = {};
     double sv = 0.0;   // with cfl: the cell's rate sum_d (|u_d| + c) / dx_d of Eq. 17 (interior cells)
     if (idx < g.cells) {
         int x, y, z;
@@ -203,7 +205,7 @@ __global__ __launch_bounds__(256) void k_prims(const double *U, double *__restri
                 if (g.nz > 1) v += (fabs(u[NS + 2] * rinv) + c) * g.idz;
                 if (v > sv) sv = v;   // NaN never wins (it is flagged)
             }
-            if constexpr (GLF) {
+            if (GLF && glf) {
                 const bool in[3] = {x >= g.gx && x < g.gx + g.nx, y >= g.gy && y < g.gy + g.ny,
                                     z >= g.gz && z < g.gz + g.nz};
                 const bool active[3] = {g.nx > 1, g.ny > 1, g.nz > 1};
@@ -220,7 +222,7 @@ __global__ __launch_bounds__(256) void k_prims(const double *U, double *__restri
             if (flags) atomicOr(status, flags);
         }
     }
-    if constexpr (GLF) {
+    if (GLF && glf) {
         // block maxima, then one 64-bit atomicMax each (see below).  A pass of
         // its own per direction read the state again, 27 us each at 0.7 M
         // cells where the primitives themselves take 21
